@@ -68,7 +68,9 @@ typedef enum {
 #define CC_VALIDATE 2u  /* check CSR shape, ids, lengths and (undirected) symmetry on upload */
 
 /* Traversal mode */
-#define CC_BATCHED 0    /* 64 samples per 64-bit word, all words of a node together */
+#define CC_BATCHED 0    /* 64 samples per 64-bit word, all words of a node together; small graphs (unit lengths,
+                           k <= 256, at most 49,152 nodes and 2^21 arcs) instead run one workgroup per sample,
+                           two launches an estimate, with the same results */
 #define CC_PLAIN 1      /* one sample at a time (the one-source baseline) */
 #define CC_GRAPH 0x100  /* or-ed into CC_BATCHED: capture the whole estimate as a HIP graph on the first call
                            and replay it when the same graph, k, eps, output pointers and stream come again
@@ -76,7 +78,8 @@ typedef enum {
                            A replay is checked on the host (each BFS ended within the captured levels with
                            the same deepest level; the weighted searches' largest distances within the
                            captured ones; no error flag) and otherwise the estimate is recomputed as usual,
-                           so results never depend on it.  Samples may change between calls. */
+                           so results never depend on it.  Samples may change between calls.  Small graphs
+                           (CC_BATCHED) need no capture: their two launches are made as they are. */
 
 typedef struct cc_context cc_context;
 typedef struct cc_graph cc_graph;
@@ -220,8 +223,8 @@ cc_status cc_estimate_device_noalloc(cc_context* ctx, const cc_graph* g, const c
 
 /* Several estimates in one call, for many small graphs.  outs[j] holds HOST
  * pointers for job j (graphs[j], params[j]).  Jobs on undirected graphs
- * without arc lengths, with k <= 192 and at most 131072 nodes, are traversed
- * together: their graphs are laid side by side and their samples share the
+ * without arc lengths, with k <= 192 and at most 131072 nodes, that are not
+ * small (CC_BATCHED) are traversed together: their graphs are laid side by side and their samples share the
  * bit words of one batched search (up to 256 samples, each job in whole
  * 64-bit words), so one launch per level serves every job of a batch; other
  * jobs run one by one.  Results are identical to separate calls.  statuses
@@ -231,7 +234,8 @@ cc_status cc_estimate_batch(cc_context* ctx, int32_t count, const cc_graph* cons
                             cc_result* outs, cc_status* statuses);
 
 /* Timing of the last cc_estimate / cc_estimate_device on this context, from
- * HIP events recorded on the stream the kernels ran on (milliseconds), plus
+ * HIP events recorded on the stream the kernels ran on (milliseconds; small
+ * graphs: from the device's clock read by the kernels), plus
  * the work counters the bench turns into bytes. */
 typedef struct {
     double total_ms;       /* samples on device -> all outputs in device memory */
@@ -439,7 +443,7 @@ cc_status cc_reach_weighted(cc_context* ctx, const cc_graph* g, const cc_reach_w
  * completes.  Returns CC_OK with a job handle (queued), or CC_EINVAL.  Jobs
  * are admitted onto the device as memory (cc_config.mem_budget_bytes) and
  * slots (max_inflight) free up, and run concurrently on several streams; a
- * slot that takes a small job (as in cc_estimate_batch) also takes the small
+ * slot that takes a job that cc_estimate_batch would batch also takes the small
  * jobs queued behind it that fit, into one batched traversal.  The oldest
  * queued job can be passed by younger ones that fit the memory it waits for
  * at most 16 times; then it is admitted next.  Each slot keeps its device

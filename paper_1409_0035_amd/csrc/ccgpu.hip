@@ -360,6 +360,8 @@ struct Lane {
         uint32_t wmaxd[2];  // a weighted replay: the largest distance of each direction's searches
         int32_t ids[kStagedSamples];     // the samples, internal ids (read by the traversal's first launch)
         int32_t caller[kStagedSamples];  // the same, as the caller numbers them
+        SmallRecord small[kSmallSamples];  // a small graph's searches
+        uint32_t stamps[kSmallStamps];
     };
     Readback* rb_host = nullptr;  // pinned: a replay's control block and flags, and the staged samples
     Readback* rb_dev = nullptr;   // its device-visible address
@@ -457,6 +459,7 @@ struct cc_graph {
     std::vector<int32_t> chunks_host;  // hub chunk triples (undirected graphs), for batching
     bool borrowed = false;  // the arcs (and lengths) are the caller's device arrays, never freed here
     mutable std::atomic<int32_t> bfs_hint{0};  // levels the last batched traversal of this graph ran
+    mutable std::atomic<bool> small_deep{false};  // a distance passed 254: the small-graph searches cannot hold it
     cc_tuning tune{4, 1024, 8192, 1, 1024, 64};  // launch shapes (cc_graph_set_tuning / cc_autotune)
 };
 
@@ -1297,6 +1300,160 @@ void fill_epilogue_outputs(EpilogueArgs& ea, const cc_result* out, int64_t* src_
     ea.Dout = out->D;
 }
 
+// Whether the estimate runs as one workgroup per sample (bfs_small.hip).
+bool small_search_fits(const cc_graph* gr, const Resolved& r) {
+    const DevGraph& g = gr->dg;
+    return r.mode == CC_BATCHED && !g.weighted && r.k <= kSmallSamples && g.n <= kSmallNodes &&
+           g.arcs <= kSmallArcs && !gr->small_deep.load(std::memory_order_relaxed);
+}
+
+double wall_clock_khz(int device) {
+    static std::atomic<int> rate{0};
+    int khz = rate.load(std::memory_order_relaxed);
+    if (khz == 0) {
+        if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) khz = 100000;
+        rate.store(khz, std::memory_order_relaxed);
+    }
+    return khz;
+}
+
+// A small graph's estimate: two launches, no copies; the searches report into
+// the lane's pinned memory.  False when the general path has to run it (a
+// distance beyond 254, or the allocation-free lane's buffers too small).
+bool run_small(cc_context* ctx, const cc_graph* gr, const Resolved& r, const std::vector<int32_t>& samples_int,
+               const cc_result* out, Lane& L, cc_timing* timing, cc_status* result) {
+    const DevGraph& g = gr->dg;
+    const int32_t n = (int32_t)g.n, k = r.k, npad = (n + 63) / 64 * 64, W = (k + 63) / 64;
+    const bool want_err = out->S_err || out->S_ad || out->S_ad_err || out->S_sweep || out->S_sweep_err;
+    const size_t rows = want_err ? (size_t)n * k : 0;
+    const size_t need = Carver::sz((size_t)k * npad) + Carver::sz((size_t)k * k) +
+                        Carver::sz(sizeof(uint64_t) * (size_t)k * kSmallT * W) + Carver::sz(sizeof(int32_t) * k) * 2 +
+                        Carver::sz(sizeof(int32_t) * (size_t)k * kSmallT) +
+                        Carver::sz(sizeof(int64_t) * (size_t)k * kSmallT) + Carver::sz(sizeof(int64_t) * k) +
+                        Carver::sz(rows) + Carver::sz(want_err ? sizeof(int32_t) * n : 0) + Carver::sz(sizeof(DevFlags)) +
+                        (want_err ? Carver::sz(sweep_scratch_bytes(n, k)) : 0);
+    if (L.no_alloc && need > L.arena.size) return false;
+    hipStream_t st = L.stream;
+    Carver c(L.arena.get(need));
+    SmallArgs a;
+    a.n = n;
+    a.npad = npad;
+    a.k = k;
+    a.arcs = (uint32_t)g.arcs;
+    a.in_rp = g.rrp;
+    a.in_col = g.rcol;
+    a.out_rp = g.rp;
+    a.out_col = g.col;
+    a.orig = g.orig;
+    a.Dt = c.take<uint8_t>((size_t)k * npad);
+    a.dmat_c = c.take<uint8_t>((size_t)k * k);
+    a.lmask = c.take<uint64_t>((size_t)k * kSmallT * W);
+    a.rmax = c.take<int32_t>(k);
+    a.Tcnt = c.take<int32_t>((size_t)k * kSmallT);
+    a.Tsum = c.take<int64_t>((size_t)k * kSmallT);
+    a.src_sum = c.take<int64_t>(k);
+    a.status = c.take<int32_t>(k);
+    a.rec = L.rb_dev->small;
+    a.stamps = L.rb_dev->stamps;
+    a.flags = &L.rb_dev->flags;
+    a.en = r.en;
+    a.ed = r.ed;
+    SmallOut o;
+    o.S_hyb = out->S_hyb;
+    o.S_samp = out->S_samp;
+    o.S_piv = out->S_piv;
+    o.S_pub = out->S_pub;
+    o.pivot = out->pivot;
+    o.delta = out->delta;
+    o.sampsum = out->sampsum;
+    o.src_sum = out->src_sum;
+    o.samples = out->samples;
+    o.dmat = out->dmat;
+    o.D = out->D;
+    o.rows = want_err ? c.take<uint8_t>(rows) : nullptr;
+    o.sidx = want_err ? c.take<int32_t>(n) : nullptr;
+    DevFlags* err_flags = c.take<DevFlags>(1);
+    SmallSamples ss;
+    std::memcpy(ss.ids, samples_int.data(), sizeof(int32_t) * k);
+    std::memcpy(ss.caller, r.samples.data(), sizeof(int32_t) * k);
+    CCG_HIP(hipStreamSynchronize(st));  // the lane's earlier launches are done with its pinned memory
+    L.rb_host->flags = DevFlags{};
+    for (int32_t i = 0; i < k; i++) L.rb_host->small[i].state = 3;  // a report that did not land
+    small_estimate(st, a, o, ss, g.directed);
+    CCG_HIP(hipStreamSynchronize(st));
+    int32_t ecc = 0, levels = 0, bad = 0;
+    int64_t arcs = 0;
+    const uint32_t first = L.rb_host->small[0].start;  // differences of low words: the searches take far less than 2^32 ticks
+    int32_t begin = 0, mid = 0, last = 0;
+    for (int32_t i = 0; i < k; i++) {
+        const SmallRecord& q = L.rb_host->small[i];
+        const int32_t status = (int32_t)(q.state & 15);
+        if (status == 3) throw HipError{hipErrorUnknown, "a small graph's search did not report"};
+        bad = std::max(bad, status == 1 ? 3 : status);  // unreached nodes before depth
+        ecc = std::max(ecc, (int32_t)(q.state >> 4 & 0xFFF));
+        levels = std::max(levels, (int32_t)(q.state >> 16));
+        arcs += q.arcs;
+        begin = std::min(begin, (int32_t)(q.start - first));
+        mid = std::max(mid, (int32_t)(q.end - first));
+    }
+    if (bad == 3) {
+        *result = fail(CC_EDISCONNECTED, "some node is unreachable from some sample");
+        return true;
+    }
+    if (bad == 2) {
+        gr->small_deep.store(true, std::memory_order_relaxed);
+        return false;
+    }
+    for (int32_t q = 0; q < std::min(kSmallStamps, npad / 64); q++)
+        last = std::max(last, (int32_t)(L.rb_host->stamps[q] - first));
+    DevFlags hf = L.rb_host->flags;
+    if (want_err) {
+        ErrArgs ea;
+        ea.D = o.rows;
+        ea.dk = DistKind::U8;
+        ea.n = n;
+        ea.k = k;
+        ea.sidx = o.sidx;
+        ea.orig = g.orig;
+        ea.dmat_c = a.dmat_c;
+        ea.mt_bytes = 1;
+        ea.Tcnt = a.Tcnt;
+        ea.Tsum = a.Tsum;
+        ea.tlen = kSmallT;
+        ea.src_sum = a.src_sum;
+        ea.eps_num = r.en;
+        ea.eps_den = r.ed;
+        ea.S_err = out->S_err;
+        ea.S_ad = out->S_ad;
+        ea.S_ad_err = out->S_ad_err;
+        ea.S_sweep = out->S_sweep;
+        ea.S_sweep_err = out->S_sweep_err;
+        ea.sweep_scratch = c.take<char>(sweep_scratch_bytes(n, k));
+        fill_u32(st, err_flags, 0u, sizeof(DevFlags) / 4);
+        run_errest(st, ea, err_flags);
+        DevFlags ef;
+        CCG_HIP(hipMemcpyAsync(&ef, err_flags, sizeof(ef), hipMemcpyDeviceToHost, st));
+        CCG_HIP(hipStreamSynchronize(st));
+        hf.overflow |= ef.overflow;
+        hf.disconnected |= ef.disconnected;
+    }
+    L.last_maxd = ecc;
+    if (timing) {
+        const double khz = wall_clock_khz(ctx->device);
+        *timing = cc_timing{};
+        timing->traverse_ms = timing->kernel_ms = (double)(mid - begin) / khz;
+        timing->epilogue_ms = last > mid ? (double)(last - mid) / khz : 0.0;
+        timing->total_ms = timing->traverse_ms + timing->epilogue_ms;
+        timing->levels = levels;
+        timing->arcs_scanned = arcs;
+        timing->nodes_visited = (int64_t)n * k;
+        timing->launches = timing->kernel_launches = 1;
+        timing->dist_bytes = 1;
+    }
+    *result = finish_flags(hf);
+    return true;
+}
+
 // Runs the whole pipeline on lane `L`; `out` holds DEVICE pointers (caller's node ids).
 cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const cc_result* out, Lane& L,
                   cc_timing* timing) {
@@ -1307,6 +1464,10 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
     hipStream_t st = L.stream;
     std::vector<int32_t> samples_int((size_t)k);
     for (int32_t i = 0; i < k; i++) samples_int[(size_t)i] = gr->inv[(size_t)r.samples[(size_t)i]];
+    if (small_search_fits(gr, r)) {
+        cc_status small_result = CC_OK;
+        if (run_small(ctx, gr, r, samples_int, out, L, timing, &small_result)) return small_result;
+    }
 
     // small per-job buffers
     const size_t small = Carver::sz(sizeof(int32_t) * k) + Carver::sz(sizeof(DevFlags)) +
@@ -1992,9 +2153,9 @@ struct Staging {
         dev.S_sweep = (double*)dptr(host->S_sweep);
         dev.S_sweep_err = (double*)dptr(host->S_sweep_err);
     }
+    // the fields lie one after the other on both sides: one copy brings them all
     void to_pinned(hipStream_t st, char* pbase) const {
-        for (const auto& f : fields)
-            CCG_HIP(hipMemcpyAsync(pbase + f.off, f.d, f.bytes, hipMemcpyDeviceToHost, st));
+        if (!fields.empty()) CCG_HIP(hipMemcpyAsync(pbase, fields.front().d, total, hipMemcpyDeviceToHost, st));
     }
     void deliver(const char* pbase) const {
         for (const auto& f : fields) std::memcpy(f.h, pbase + f.off, f.bytes);
@@ -2029,7 +2190,8 @@ constexpr int32_t kMaxOvertakes = 16;          // younger jobs that may pass a w
 constexpr int32_t kBatchWords = 4;
 
 bool batchable(const cc_graph* g, const Resolved& r) {
-    return !g->borrowed && !g->dg.directed && !g->dg.weighted && r.mode == CC_BATCHED && r.k <= 192 && g->dg.n <= kBatchNodeLimit &&
+    // a small graph's own two launches cost less than its share of a shared traversal
+    return !small_search_fits(g, r) && !g->borrowed && !g->dg.directed && !g->dg.weighted && r.mode == CC_BATCHED && r.k <= 192 && g->dg.n <= kBatchNodeLimit &&
            g->dg.arcs < ((int64_t)1 << 30);
 }
 

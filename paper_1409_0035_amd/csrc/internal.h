@@ -503,6 +503,70 @@ void run_bits_epilogue(hipStream_t st, const BitsEpilogueArgs& a, void* scratch,
 
 void fill_u32(hipStream_t st, void* p, uint32_t value, size_t count);
 
+// Small graphs with unit lengths (bfs_small.hip): every sample's search and
+// tables in one launch, a workgroup a sample, and every estimate in a second.
+constexpr int32_t kSmallSamples = 256;
+constexpr int32_t kSmallT = 256;       // entries of a sample's tail tables: distances 0..254 and the empty tail
+constexpr int32_t kSmallStamps = 64;
+// The graphs searched that way: one distance byte a node, the visited bits and
+// the frontier fit LDS up to 65,536 nodes; the line lies lower, where the
+// bit-parallel search's replays draw level (k = 64, replays against this
+// path's calls: preferential attachment 20,000 nodes 193 against 104 us,
+// 40,000 nodes 210 / 176, 65,536 nodes 224 / 252; R-MAT scale 15 189 / 126,
+// scale 16 (47,000 nodes, 1.9 M arcs) 220 / 208; round trips on directed R-MAT
+// scale 15 329 / 169, scale 16 356 / 266, scale 17 (55,000 nodes) 345 / 472).
+constexpr int64_t kSmallNodes = 49152;
+constexpr int64_t kSmallArcs = (int64_t)1 << 21;
+// What a search reports, in pinned host memory.
+struct alignas(16) SmallRecord {
+    uint32_t state;       // bits 0-3: 0 every node reached, 1 some not, 2 a distance beyond 254;
+                          // 4-15: the largest distance (of a round trip: a bound on it); 16-31: levels run
+    uint32_t arcs;        // arcs visited
+    uint32_t start, end;  // low words of the wall clock
+};
+struct SmallSamples {
+    int32_t ids[kSmallSamples];     // internal ids
+    int32_t caller[kSmallSamples];  // the caller's
+};
+struct SmallArgs {
+    int32_t n = 0, npad = 0, k = 0;  // npad: n rounded up to 64
+    int32_t qcap = 0;                // frontier entries (set by small_estimate)
+    uint32_t arcs = 0;
+    const uint32_t* in_rp = nullptr;
+    const int32_t* in_col = nullptr;
+    const uint32_t* out_rp = nullptr;
+    const int32_t* out_col = nullptr;
+    const int32_t* orig = nullptr;
+    uint8_t* Dt = nullptr;       // [k][npad] distances, source-major
+    uint8_t* dmat_c = nullptr;   // [k][k]
+    uint64_t* lmask = nullptr;   // [k][kSmallT][W]
+    int32_t* rmax = nullptr;     // [k] largest entry of a row of dmat_c
+    int32_t* Tcnt = nullptr;     // [k][kSmallT]
+    int64_t* Tsum = nullptr;
+    int64_t* src_sum = nullptr;  // [k]
+    int32_t* status = nullptr;   // [k]
+    SmallRecord* rec = nullptr;  // [k] pinned
+    uint32_t* stamps = nullptr;  // [kSmallStamps] pinned: when the estimates were done
+    DevFlags* flags = nullptr;   // pinned, cleared by the host
+    int64_t en = 1, ed = 1;
+};
+struct SmallOut {  // device, at the caller's ids; each may be null
+    double* S_hyb = nullptr;
+    double* S_samp = nullptr;
+    int64_t* S_piv = nullptr;
+    int64_t* S_pub = nullptr;
+    int32_t* pivot = nullptr;
+    int32_t* delta = nullptr;
+    int64_t* sampsum = nullptr;
+    int64_t* src_sum = nullptr;
+    int32_t* samples = nullptr;
+    int32_t* dmat = nullptr;
+    int32_t* D = nullptr;
+    uint8_t* rows = nullptr;  // [n][k] byte rows, internal order (the error pass)
+    int32_t* sidx = nullptr;  // [n] sample index or -1, internal order
+};
+void small_estimate(hipStream_t st, SmallArgs a, const SmallOut& o, const SmallSamples& ss, bool round_trip);
+
 // Node-weighted hybrid estimate (Sec. 5, Algorithm 3) from int32 distance
 // rows at the caller's ids.
 struct BetaArgs {

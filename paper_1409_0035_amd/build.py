@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libccgpu.so")
-SOURCES = ["ccgpu.hip", "bfs_batched.hip", "bfs_small.hip", "bfs_plain.hip", "sssp_weighted.hip", "epilogue.hip", "epilogue_bits.hip",
+SOURCES = ["ccgpu.hip", "bfs_batched.hip", "bfs_small.hip", "bfs_plain.hip", "sssp_weighted.hip", "sssp_patch.hip", "epilogue.hip", "epilogue_bits.hip",
            "reach.hip", "epilogue_beta.hip", "prio.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

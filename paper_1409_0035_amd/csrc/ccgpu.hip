@@ -314,6 +314,12 @@ __global__ void k_wstatus_out(const uint32_t* __restrict__ flags, const uint32_t
     else if (t < nf + 2) __hip_atomic_store(maxd_host + (t - nf), maxd[t - nf], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Share of a weighted graph's arcs inside patches from which it is searched by
+// them.  Grids of degree 4-8 lie at 0.91 (2048 x 2048, 64 samples: 48 ms
+// against 136); preferential attachment, R-MAT and uniform random graphs of
+// 4-13 arcs a node lie at 0.16-0.31, where most relaxations would be offers and
+// patches have too many neighbours.  No generator here falls between.
+constexpr double kPatchInside = 0.6;
 constexpr int32_t kStagedSamples = 256;  // samples of an estimate that can be replayed from a captured graph
 
 struct Lane {
@@ -452,13 +458,15 @@ struct cc_graph {
     DevGraph dg;
     uint32_t flags = 0;
     std::atomic<int> refs{1};
-    void* mem[12] = {};
+    void* mem[32] = {};
     size_t bytes = 0;
     std::vector<int32_t> inv;  // caller's id -> internal id
     uint64_t id = 0;  // never reused: keys captured estimates
     std::vector<int32_t> chunks_host;  // hub chunk triples (undirected graphs), for batching
     bool borrowed = false;  // the arcs (and lengths) are the caller's device arrays, never freed here
     mutable std::atomic<int32_t> bfs_hint{0};  // levels the last batched traversal of this graph ran
+    mutable std::atomic<int32_t> patch_hint[2] = {{0}, {0}};  // rounds the last searches by patches ran, by direction
+    mutable std::atomic<bool> patch_off{false};  // distances too large, or too many rounds, for the searches by patches
     mutable std::atomic<bool> small_deep{false};  // a distance passed 254: the small-graph searches cannot hold it
     cc_tuning tune{4, 1024, 8192, 1, 1024, 64};  // launch shapes (cc_graph_set_tuning / cc_autotune)
 };
@@ -742,6 +750,60 @@ void transpose_host(int64_t n, const std::vector<uint32_t>& rp, const std::vecto
 }
 }  // namespace
 
+// Cuts a graph into patches of up to kPatchNodes nodes, grown breadth-first
+// from the lowest id left (so a row-major grid gets near-squares): order lists
+// the nodes patch by patch, pstart where each begins.  False when too few
+// arcs would stay inside (denser or unlocal graphs), which the first patches
+// show.
+static bool grow_patches(int64_t n, const int64_t* rp, const int32_t* col, std::vector<int32_t>& order,
+                         std::vector<int32_t>& pstart) {
+    constexpr int64_t kLook = 64 * kPatchNodes;  // nodes after which the share is first looked at
+    if (n < 2 * kPatchNodes || rp[n] > 12 * n) return false;
+    order.clear();
+    order.reserve((size_t)n);
+    pstart.assign(1, 0);
+    std::vector<int32_t> patch((size_t)n, -1);
+    auto inside = [&]() {  // arcs of the patches so far that stay in their patch, against all of theirs
+        int64_t in = 0, all = 0;
+        for (int32_t v : order)
+            for (int64_t e = rp[v]; e < rp[v + 1]; e++) {
+                all++;
+                in += patch[(size_t)col[e]] == patch[(size_t)v];
+            }
+        return all == 0 ? 0.0 : (double)in / (double)all;
+    };
+    int64_t seed = 0;
+    bool looked = false;
+    while ((int64_t)order.size() < n) {
+        const int32_t id = (int32_t)pstart.size() - 1;
+        const size_t begin = order.size();
+        size_t head = begin;
+        for (;;) {
+            if (head == order.size()) {  // the region is full or closed in
+                if (order.size() - begin >= kPatchNodes / 4) break;
+                while (seed < n && patch[(size_t)seed] >= 0) seed++;
+                if (seed == n) break;
+                patch[(size_t)seed] = id;
+                order.push_back((int32_t)seed);
+            }
+            const int32_t u = order[head++];
+            for (int64_t e = rp[u]; e < rp[u + 1] && order.size() - begin < kPatchNodes; e++) {
+                const int32_t v = col[e];
+                if (patch[(size_t)v] >= 0) continue;
+                patch[(size_t)v] = id;
+                order.push_back(v);
+            }
+            if (order.size() - begin >= kPatchNodes) break;
+        }
+        pstart.push_back((int32_t)order.size());
+        if (!looked && (int64_t)order.size() >= kLook) {
+            looked = true;
+            if (inside() < kPatchInside) return false;
+        }
+    }
+    return looked || inside() >= kPatchInside;
+}
+
 // The (end, length) pairs the batched weighted searches read, for both
 // directions, into library-owned slots a and b.
 static void zip_weighted(cc_graph* g, int a, int b, hipStream_t st) {
@@ -794,8 +856,15 @@ extern "C" cc_status cc_graph_upload(cc_context* ctx, int64_t n, int64_t arcs, c
             for (int64_t e = 0; e < arcs; e++) deg[(size_t)col_idx[e]]++;
         std::vector<int32_t> orig((size_t)n);
         for (int64_t v = 0; v < n; v++) orig[(size_t)v] = (int32_t)v;
-        // weighted graphs keep the caller's order (delta-stepping works on
-        // (sample, node) pairs and profits from the input's own locality)
+        // weighted graphs go by patches where they can be cut into them; the
+        // others keep the caller's order (delta-stepping works on (sample,
+        // node) pairs and profits from the input's own locality)
+        std::vector<int32_t> pstart;
+        if (w) {
+            std::vector<int32_t> order;
+            if (grow_patches(n, row_ptr, col_idx, order, pstart)) orig.swap(order);
+            else pstart.clear();
+        }
         if (!w)
             std::stable_sort(orig.begin(), orig.end(),
                              [&](int32_t a, int32_t b) { return deg[(size_t)a] > deg[(size_t)b]; });
@@ -910,6 +979,29 @@ extern "C" cc_status cc_graph_upload(cc_context* ctx, int64_t n, int64_t arcs, c
             g->dg.n_hub_chunks_out = g->dg.n_hub_chunks_in;
         }
         if (w) zip_weighted(g, 10, 11, nullptr);
+        if (!pstart.empty()) {
+            PatchGraph& pg = g->dg.patches;
+            int slot = 14;
+            auto take = [&](size_t bytes) -> void* {
+                void* d = nullptr;
+                if (hipMalloc(&d, bytes) != hipSuccess) {
+                    (void)hipGetLastError();
+                    throw std::bad_alloc();
+                }
+                g->mem[slot++] = d;
+                g->bytes += bytes;
+                return d;
+            };
+            pg.npatch = (int32_t)pstart.size() - 1;
+            pg.pstart = (const int32_t*)up(12, pstart.data(), sizeof(int32_t) * pstart.size());
+            int32_t* of = (int32_t*)take(sizeof(int32_t) * (size_t)n);
+            pg.patch_of = of;
+            build_patch_of(nullptr, pg.npatch, pg.pstart, of);
+            bool ok = build_patch_arcs(nullptr, pg, 0, g->dg.rp, g->dg.cw, take);
+            if (ok && directed) ok = build_patch_arcs(nullptr, pg, 1, g->dg.rrp, g->dg.rcw, take);
+            else if (ok) pg.dir[1] = pg.dir[0];
+            if (!ok) pg = PatchGraph{};  // a patch with too many neighbours: searched without patches
+        }
     } catch (const std::bad_alloc&) {
         graph_unref(g);
         return fail(CC_ENOMEM, "cc_graph_upload: device allocation failed");
@@ -1509,9 +1601,16 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
         }
         // weighted batched searches of up to 256 samples in one launch per direction can be captured
         const bool w_single = g.weighted && mode != CC_PLAIN && kw >= k && k <= kStagedSamples;
+        bool patched = g.weighted && mode != CC_PLAIN && g.patches.npatch > 0 &&
+                       !gr->patch_off.load(std::memory_order_relaxed);
+        if (patched) kw = std::min(kw, kPatchSamples);
+        // the patches' rounds reach 16 bucket widths past a sample's least wait
+        const uint32_t patch_step = (uint32_t)std::min<int64_t>(16 * (int64_t)std::max(1, gr->tune.delta), INT32_MAX);
         size_t trav_scratch;
         if (g.weighted)
-            trav_scratch = mode == CC_PLAIN ? sssp_weighted_scratch(n, 1) : sssp_wsearch_scratch(n, kw);
+            trav_scratch = mode == CC_PLAIN ? sssp_weighted_scratch(n, 1)
+                           : patched        ? std::max(sssp_wsearch_scratch(n, kw), patch_scratch(kw, g.patches.npatch))
+                                            : sssp_wsearch_scratch(n, kw);
         else
             trav_scratch = mode == CC_PLAIN ? bfs_plain_scratch(n, g.arcs, k) : bfs_batched_scratch(n, kg0, g.nh);
         const size_t hist_elems = bits_path ? (size_t)kHistSlotsBatched * k * cap : 0;
@@ -1700,8 +1799,19 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                     shape.delta = (uint32_t)std::max(1, gr->tune.delta);
                     shape.round_blocks = gr->tune.round_blocks;
                     shape.local_passes = gr->tune.local_passes;
-                    const int wr =
-                        mode == CC_PLAIN
+                    int wr = 0;
+                    if (patched) {
+                        int32_t hint = gr->patch_hint[dir].load(std::memory_order_relaxed);
+                        wr = sssp_patch(st, g.patches, dir, n, samples_dev + s0, kg, (uint32_t*)Dt + (size_t)s0 * n,
+                                        patch_step, ts, trav_scratch, &hint, &md, &ds);
+                        gr->patch_hint[dir].store(hint, std::memory_order_relaxed);
+                        if (wr == 4) {  // near the limit of distances, or too deep: as without patches
+                            patched = false;
+                            gr->patch_off.store(true, std::memory_order_relaxed);
+                        }
+                    }
+                    if (!patched)
+                        wr = mode == CC_PLAIN
                             ? sssp_weighted(st, out_rp, out_col, wv, n, samples_dev + s0, kg,
                                             (uint32_t*)Dt + (size_t)s0 * n, shape, ts, trav_scratch, &md, &ds)
                             : sssp_weighted_batched(st, out_rp, dir == 0 ? g.cw : g.rcw, n, samples_dev + s0, kg,
@@ -1897,9 +2007,17 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                                    (const int32_t*)L.rb_dev->caller, k, samples_dev, out->samples);
                 compute_sidx(st, samples_dev, k, sidx, n);
                 for (int dir = 0; dir < (g.directed ? 2 : 1); dir++) {
-                    sssp_weighted_batched_enqueue(st, dir == 0 ? g.rp : g.rrp, dir == 0 ? g.cw : g.rcw, n, samples_dev,
-                                                  k, (uint32_t*)Dt, (uint32_t)std::max(1, gr->tune.delta), ts,
-                                                  trav_scratch, flags, wmaxd_dev + dir);
+                    if (patched) {
+                        // a quarter more rounds than this search ran: other samples' searches reach about as far
+                        const int32_t ran = gr->patch_hint[dir].load(std::memory_order_relaxed);
+                        sssp_patch_enqueue(st, g.patches, dir, n, samples_dev, k, (uint32_t*)Dt, patch_step, ts,
+                                           trav_scratch, ran + ran / 4 + 4, flags, wmaxd_dev + dir);
+                    } else {
+                        sssp_weighted_batched_enqueue(st, dir == 0 ? g.rp : g.rrp, dir == 0 ? g.cw : g.rcw, n,
+                                                      samples_dev, k, (uint32_t*)Dt,
+                                                      (uint32_t)std::max(1, gr->tune.delta), ts, trav_scratch, flags,
+                                                      wmaxd_dev + dir);
+                    }
                     transpose_dist(st, Dt, dir == 0 ? D : Dr, n, k, dk);
                 }
                 run_epilogue(st, ea, ea_scratch, ea_es, flags);

@@ -135,6 +135,29 @@ template <> struct DistT<uint32_t> {
 };
 
 // ---------------------------------------------------------------- graph
+// Patches of a weighted graph (sssp_patch.hip): consecutive internal ids, at
+// most kPatchNodes a patch, with the arcs of each direction split into those
+// that stay inside (kPatchSlots a node) and the others.
+constexpr int kPatchNodes = 256;
+constexpr int kPatchSlots = 8;
+constexpr int kPatchNb = 32;  // neighbouring patches, and a patch's own slot
+constexpr int32_t kPatchRounds = 16384;
+constexpr int32_t kPatchSamples = 512;  // per call: eight groups of at most a wave's lanes
+struct PatchDir {
+    const uint32_t* ell = nullptr;  // [npatch][kPatchSlots][kPatchNodes] weight << 8 | end within the patch
+    const int32_t* eptr = nullptr;  // [npatch + 1] a patch's outside arcs in ext
+    const uint4* ext = nullptr;     // (end, weight, start within the patch | place of its patch in `to` << 8, end's patch)
+    const int32_t* iptr = nullptr;  // [npatch + 1] the outside arcs into a patch, in `in`
+    const uint4* in = nullptr;      // (start, weight, end within the patch, start's patch); null: ext reversed
+    const int64_t* to = nullptr;    // [npatch][kPatchNb] neighbouring patch << 8 | this patch's slot there, -1: none
+};
+struct PatchGraph {
+    int32_t npatch = 0;  // 0: the graph has no patches
+    const int32_t* pstart = nullptr;    // [npatch + 1]
+    const int32_t* patch_of = nullptr;  // [n]
+    PatchDir dir[2];  // 0 over the out-arcs, 1 over the in-arcs
+};
+
 // Device copy of a graph in the library's internal node order: ids sorted by
 // degree, largest first (the "graph builder" step of the upload).
 struct DevGraph {
@@ -165,6 +188,7 @@ struct DevGraph {
     // graphs kept in the caller's order (borrowed device CSRs): the 64-node
     // groups that hold a high-degree node, flagged, instead of the prefix [0, nh)
     const uint8_t* ghub = nullptr;
+    PatchGraph patches;  // weighted graphs that can be cut into patches
 };
 
 // The adjacency one batched traversal uses: pull over rp/col (in-arcs), push
@@ -358,6 +382,17 @@ size_t sssp_wsearch_scratch(int64_t n, int32_t kg);
 void sssp_weighted_batched_enqueue(hipStream_t st, const uint32_t* rp, const int2* cw, int64_t n,
                                    const int32_t* samples_dev, int32_t kg, uint32_t* Dt, uint32_t delta,
                                    void* scratch, size_t scratch_size, DevFlags* flags, uint32_t* maxd_out);
+// The same searches patch by patch (sssp_patch.hip)
+void build_patch_of(hipStream_t st, int32_t npatch, const int32_t* pstart, int32_t* patch_of);
+bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, const int2* cw,
+                      const std::function<void*(size_t)>& alloc);
+size_t patch_scratch(int32_t kg, int32_t npatch);
+int sssp_patch(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const int32_t* samples_dev, int32_t kg,
+               uint32_t* Dt, uint32_t step, void* scratch, size_t scratch_size, int32_t* hint, int64_t* maxd,
+               TravStats* stats);
+void sssp_patch_enqueue(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const int32_t* samples_dev, int32_t kg,
+                        uint32_t* Dt, uint32_t step, void* scratch, size_t scratch_size, int32_t count,
+                        DevFlags* flags, uint32_t* maxd_out);
 // (end, length) pairs of a weighted adjacency, for the batched searches
 void zip_arcs(hipStream_t st, const int32_t* col, const int32_t* w, int64_t arcs, int2* out);
 

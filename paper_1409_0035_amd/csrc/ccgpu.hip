@@ -1945,6 +1945,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
             ea.dk = dk;
             ea.D = D;
             ea.Dr = rt_summed ? nullptr : Dr;
+            ea.Dt = g.weighted && !g.directed ? (const uint32_t*)Dt : nullptr;
             ea.samples = samples_dev;
             ea.sidx = sidx;
             ea.orig = g.orig;

@@ -403,6 +403,7 @@ struct EpilogueArgs {
     DistKind dk = DistKind::U8;
     const void* D = nullptr;     // node-major distances, internal node order
     const void* Dr = nullptr;    // reverse-direction distances (round trip) or nullptr
+    const uint32_t* Dt = nullptr;  // the same distances source-major, Dt[i][v] (arc lengths, one direction), or null
     const int32_t* samples = nullptr;  // device, internal ids
     const int32_t* sidx = nullptr;     // device, internal id -> sample index or -1
     const int32_t* orig = nullptr;     // device, internal id -> caller's id

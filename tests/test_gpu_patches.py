@@ -1,8 +1,8 @@
 """Weighted graphs that can be cut into patches are searched patch by patch:
 every output at the edges of that path (the smallest graphs, nodes with more
 inner arcs than slots, arc lengths too large for a slot, arcs whose two
-directions differ, distances near the 31-bit limit, many samples) against the
-oracle.  Distances and sums are integers, the estimates one division of exact
+directions differ, distances near the 31-bit limit, many samples) and of the
+histogram over its rows (ranges of LDS bins) against the oracle.  Distances and sums are integers, the estimates one division of exact
 integers on both sides, so all must be identical."""
 import sys
 
@@ -38,6 +38,14 @@ def _long_path(n, w):
     return graphgen.csr_from_arcs(n, i, i + 1, np.full(n - 1, w, np.int32))
 
 
+def _two_lengths(longest):
+    """A path of 603 nodes whose length from end to end is `longest`."""
+    i = np.arange(602, dtype=np.int32)
+    w = np.full(602, longest // 602, np.int32)
+    w[: longest % 602] += 1
+    return graphgen.csr_from_arcs(603, i, i + 1, w)
+
+
 def _one_way_grid():
     return graphgen.with_lengths(graphgen.symmetric_digraph(graphgen.grid(30, 41, 4)), 1, 50, 8)
 
@@ -52,6 +60,12 @@ CASES = {
     "grid25x40-unit-like": (lambda: _grid(25, 40, 1, 2), 33),
     "caterpillar-many-inner-arcs": (lambda: _caterpillar(200, 11), 40),
     "one-way-grid-round-trip": (_one_way_grid, 50),
+    # the distance table one bin short of, at and past a range of LDS bins, and past the last range that is read again
+    "table-36863": (lambda: _two_lengths(36862), 30),
+    "table-36864": (lambda: _two_lengths(36863), 30),
+    "table-36865": (lambda: _two_lengths(36864), 30),
+    "table-20-ranges": (lambda: _two_lengths(20 * 36864 - 1), 9),
+    "table-past-20-ranges": (lambda: _two_lengths(20 * 36864), 9),
     "path-near-the-limit": (lambda: _long_path(600, 3_580_000), 3),
 }
 
@@ -62,6 +76,9 @@ def test_patches_match_oracle(name):
     g = make()
     rg = graphgen.transpose(g) if g.directed else None
     samples = np.asarray(oracle.draw_samples(g.n, k, 3), dtype=np.int32)
+    given = None
+    if name.startswith("table"):
+        given = samples = np.unique(np.concatenate([[0, g.n - 1], samples])).astype(np.int32)
     ref = oracle.estimate_all(g, samples, threads=8, reverse_graph=rg)
     out = LONG if "wide" in name or "limit" in name else OUT
     with cc.Context(0) as ctx:
@@ -69,7 +86,7 @@ def test_patches_match_oracle(name):
         for call in range(2):  # the second call enqueues the rounds of the first at once
             print(f"  {g.name}: n={g.n} arcs={g.arcs} k={k} call {call}", flush=True)
             sys.stdout.flush()
-            res = cc.cc_estimate(ctx.handle, gh, k, seed=3, outputs=out)
+            res = cc.cc_estimate(ctx.handle, gh, len(samples), seed=3, samples=given, outputs=out)
             for f in out:
                 if f in ref:
                     assert np.array_equal(res[f], np.asarray(ref[f]).astype(res[f].dtype).reshape(res[f].shape)), f

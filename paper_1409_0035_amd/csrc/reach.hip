@@ -764,7 +764,12 @@ __global__ void k_rch_rank(const int32_t* __restrict__ order_internal, int64_t n
 // membership on, as above) searches at once, one workgroup per source: the
 // near/far delta-stepping of the estimate's weighted searches on the
 // source's own row of 64-bit words 4d + flags (bit 0: in a near pile, bit 1:
-// in the far pile).  A search does not enter a node that holds more than k
+// in the far pile).  The first batch, when no node holds enough members yet, is
+// nearly all of the time; its searches were bound by hubs (one lane group
+// walked a hub's arcs, thousands of round trips in a row), by atomics that
+// improved nothing and by buckets too wide for dense graphs: R-MAT, 2^15 nodes
+// with lengths to 1000, k = 64: 30 ms; hubs spread over the workgroup 20, a
+// look before the atomic 14, the bucket width below 6.5.  A search does not enter a node that holds more than k
 // members ranked before the batch (counting the node itself when it ranks
 // before it): every node that reaches such a node through it has k members
 // ranked before every source of the batch, so it needs none of them, and
@@ -781,6 +786,18 @@ constexpr int kLBlock = 1024;  // threads per source's workgroup
 constexpr int kLGroup = 8;     // lanes per node
 constexpr int kLUnroll = 4;    // nodes a lane group has in flight
 constexpr int kLLq = 4096;     // near-pile entries kept in LDS
+constexpr uint32_t kLBig = 64; // arcs past which a node's are spread over the workgroup's waves
+constexpr int kLBigs = 1024;   // such nodes a phase; the others are walked by their lane group
+// Bucket width.  A bucket that is too wide relaxes arcs again and again (R-MAT,
+// 2^15 nodes, 14 arcs a node, 128 sources: 165 M relaxations at the graph's
+// delta, 62 M at a sixteenth of it, which is about each arc once), one that is
+// too narrow pays for phases (150 x 200 grid: 4.6 ms at delta, 12.5 ms at a
+// sixteenth).  So a search starts narrow and lets the width follow the entries
+// that a bucket took: below kLWorkLow, which a phase of 512 nodes in flight
+// hardly feels, the next is twice as wide (up to delta), above kLWorkHigh half
+// as wide.  R-MAT 6.5 ms, the grid 4.6 ms; starting at a 64th 8.5 ms and 4.6.
+constexpr int kLWorkHigh = 4096, kLWorkLow = 512;
+constexpr uint32_t kLNarrow = 256;
 constexpr int32_t kLFirstBatch = 128;
 constexpr uint64_t kLInfW = ~0ull << 2;
 constexpr uint64_t kLMaxDist = 0x7FFFFFFEull;
@@ -852,10 +869,12 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
     int32_t* fsp = V.far + (int64_t)j * 2 * n;
     __shared__ int32_t lq[2][kLLq];
     __shared__ int32_t s_cnt[2];  // entries of the next near pile; of the far pile being built
-    __shared__ int32_t s_nq, s_nf, s_qsel, s_fsel, s_stop, s_ovf, s_phases;
-    __shared__ uint32_t s_hi;
+    __shared__ int32_t s_nq, s_nf, s_qsel, s_fsel, s_stop, s_ovf, s_phases, s_nbig;
+    __shared__ int32_t s_work;            // near-pile entries taken since the bucket began
+    __shared__ uint32_t s_hi, s_width;    // the bucket's end and width
     __shared__ uint32_t s_min[kLBlock / 64];
     __shared__ unsigned long long s_relaxed;
+    __shared__ uint4 s_big[kLBigs];  // nodes with many arcs: first arc, end, distance
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int sub = lane & (kLGroup - 1), glane = lane & ~(kLGroup - 1);
     auto put_near = [&](int p, int32_t pos, int32_t v) {
@@ -870,10 +889,13 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
         s_nf = 0;
         s_qsel = 0;
         s_fsel = 0;
-        s_hi = delta;
+        s_width = max(delta / kLNarrow, 1u);
+        s_hi = s_width;
+        s_work = 0;
         s_stop = 0;
         s_ovf = 0;
         s_phases = 0;
+        s_nbig = 0;
         s_cnt[0] = s_cnt[1] = 0;
         s_relaxed = 0;
     }
@@ -882,6 +904,53 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
     const uint64_t c0 = wall_clock64();
     constexpr int kPerWave = 64 / kLGroup;
     uint64_t my_relaxed = 0;
+    // One arc a lane and step: arc a[r] (~0: none) from a node at distance d[r].
+    auto relax = [&](const uint32_t (&a)[kLUnroll], const uint64_t (&d)[kLUnroll], uint32_t hi, int pout,
+                     int32_t* fpile) {
+        int32_t u[kLUnroll];
+        uint64_t c[kLUnroll], o[kLUnroll];
+#pragma unroll
+        for (int r = 0; r < kLUnroll; r++) {
+            u[r] = -1;
+            c[r] = 0;
+            if (a[r] != ~0u) {
+                const int2 x = V.cw[a[r]];
+                u[r] = x.x;
+                c[r] = d[r] + (uint32_t)x.y;
+            }
+        }
+        // a node holding more than k members ranked before the batch takes no
+        // part, and no atomic goes to a node that has this distance already (a
+        // stale word only lets one through)
+        uint64_t have[kLUnroll];
+#pragma unroll
+        for (int r = 0; r < kLUnroll; r++) {
+            if (u[r] < 0) continue;
+            have[r] = __hip_atomic_load(&W[u[r]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if ((int64_t)V.cnt[u[r]] + (V.rank[u[r]] < t0 ? 1 : 0) > k) {
+                u[r] = -1;
+                continue;
+            }
+            my_relaxed++;
+            if (c[r] > kLMaxDist) s_ovf = 1;
+            if (c[r] >= (have[r] >> 2)) u[r] = -1;
+        }
+#pragma unroll
+        for (int r = 0; r < kLUnroll; r++) {
+            o[r] = 0;
+            if (u[r] >= 0) o[r] = rl_min(&W[u[r]], (c[r] << 2) | (c[r] < hi ? 1ull : 2ull));
+        }
+#pragma unroll
+        for (int r = 0; r < kLUnroll; r++) {
+            const bool better = u[r] >= 0 && c[r] < (o[r] >> 2);
+            const bool nr = c[r] < hi;
+            const int pn = wave_append(&s_cnt[0], better && nr && !(o[r] & 1ull));
+            if (pn >= 0) put_near(pout, pn, u[r]);
+            const int pf = wave_append(&s_cnt[1], better && !nr && !(o[r] & 2ull));
+            if (pf >= 0) fpile[pf] = u[r];
+            rl_touch(lc, V, batch, better && o[r] == kLInfW, u[r]);
+        }
+    };
     for (;;) {
         const int32_t nq = s_nq;
         const uint32_t hi = s_hi;
@@ -915,54 +984,55 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
                     d[r] = (uint64_t)__shfl((long long)d[r], glane);
                     b[r] = (uint32_t)__shfl((int)b[r], glane + 1);
                     e[r] = (uint32_t)__shfl((int)e[r], glane + 2);
-                    if (valid[r]) trips = max(trips, (e[r] - b[r] + kLGroup - 1) / kLGroup);
+                    // a node with many arcs waits for the whole workgroup, if there is room
+                    int32_t at = kLBigs;
+                    if (sub == 0 && e[r] - b[r] > kLBig) at = atomicAdd(&s_nbig, 1);
+                    at = __shfl(at, glane);
+                    if (at < kLBigs) {
+                        if (sub == 0) s_big[at] = make_uint4(b[r], e[r], (uint32_t)d[r], 0);
+                        b[r] = e[r] = 0;
+                    }
+                    trips = max(trips, (e[r] - b[r] + kLGroup - 1) / kLGroup);
                 }
 #pragma unroll
                 for (int off = 32; off > 0; off >>= 1) trips = max(trips, (uint32_t)__shfl_xor((int)trips, off));
                 for (uint32_t it = 0; it < trips; it++) {
-                    int32_t u[kLUnroll];
-                    uint64_t c[kLUnroll], o[kLUnroll];
+                    uint32_t a[kLUnroll];
 #pragma unroll
                     for (int r = 0; r < kLUnroll; r++) {
-                        const uint32_t a = b[r] + it * kLGroup + sub;
-                        u[r] = -1;
-                        c[r] = 0;
-                        if (valid[r] && a < e[r]) {
-                            const int2 x = V.cw[a];
-                            u[r] = x.x;
-                            c[r] = d[r] + (uint32_t)x.y;
-                        }
+                        a[r] = b[r] + it * kLGroup + sub;
+                        if (a[r] >= e[r]) a[r] = ~0u;
                     }
-                    // a node holding more than k members ranked before the batch takes no part
-#pragma unroll
-                    for (int r = 0; r < kLUnroll; r++)
-                        if (u[r] >= 0 && (int64_t)V.cnt[u[r]] + (V.rank[u[r]] < t0 ? 1 : 0) > k) u[r] = -1;
-#pragma unroll
-                    for (int r = 0; r < kLUnroll; r++) {
-                        o[r] = 0;
-                        if (u[r] >= 0) {
-                            my_relaxed++;
-                            if (c[r] > kLMaxDist) s_ovf = 1;
-                            o[r] = rl_min(&W[u[r]], (c[r] << 2) | (c[r] < hi ? 1ull : 2ull));
-                        }
-                    }
-#pragma unroll
-                    for (int r = 0; r < kLUnroll; r++) {
-                        const bool better = u[r] >= 0 && c[r] < (o[r] >> 2);
-                        const bool nr = c[r] < hi;
-                        const int pn = wave_append(&s_cnt[0], better && nr && !(o[r] & 1ull));
-                        if (pn >= 0) put_near(pout, pn, u[r]);
-                        const int pf = wave_append(&s_cnt[1], better && !nr && !(o[r] & 2ull));
-                        if (pf >= 0) fpile[pf] = u[r];
-                        rl_touch(lc, V, batch, better && o[r] == kLInfW, u[r]);
-                    }
+                    relax(a, d, hi, pout, fpile);
                 }
+            }
+            __syncthreads();
+            // the nodes put aside, kLUnroll x 64 arcs a wave and turn
+            const int32_t nbig = min(s_nbig, kLBigs);
+            uint32_t turn = 0;
+            for (int32_t i = 0; i < nbig; i++) {
+                const uint4 x = s_big[i];
+                const uint32_t parts = (x.y - x.x + 64 * kLUnroll - 1) / (64 * kLUnroll);
+                for (uint32_t q = (wave - turn) % (kLBlock / 64); q < parts; q += kLBlock / 64) {
+                    uint32_t a[kLUnroll];
+                    uint64_t d[kLUnroll];
+#pragma unroll
+                    for (int r = 0; r < kLUnroll; r++) {
+                        a[r] = x.x + (q * kLUnroll + r) * 64 + lane;
+                        if (a[r] >= x.y) a[r] = ~0u;
+                        d[r] = x.z;
+                    }
+                    relax(a, d, hi, pout, fpile);
+                }
+                turn += parts;
             }
             __syncthreads();
             if (threadIdx.x == 0) {
                 s_nq = s_cnt[0];
                 s_nf = s_cnt[1];
                 s_cnt[0] = 0;
+                s_nbig = 0;
+                s_work += nq;
                 s_qsel ^= 1;
                 s_phases++;
                 if (s_ovf || wall_clock64() - c0 > V.time_limit) s_stop = 1;
@@ -990,7 +1060,11 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
         __syncthreads();
         uint32_t mm = 0xFFFFFFFFu;
         for (int w = 0; w < kLBlock / 64; w++) mm = s_min[w] < mm ? s_min[w] : mm;
-        const uint64_t nh = mm > kLMaxDist ? (uint64_t)hi : ((uint64_t)mm / delta + 1) * (uint64_t)delta;
+        uint32_t width = s_width;
+        if (s_work > kLWorkHigh) width = max(width / 2, 1u);
+        else if (s_work < kLWorkLow) width = min(width, delta / 2) * 2;
+        width = max(width, 1u);
+        const uint64_t nh = mm > kLMaxDist ? (uint64_t)hi : (uint64_t)mm + width;
         const uint32_t nhi = nh > 0xFFFFFFFEull ? 0xFFFFFFFEu : (uint32_t)nh;
         int32_t* fnext = fsp + (int64_t)(s_fsel ^ 1) * n;
         for (int32_t base = wave * 64; base < nf; base += kLBlock) {
@@ -1015,6 +1089,8 @@ __global__ __launch_bounds__(kLBlock) void k_rl_search(LenCtl* lc, LenView V) {
             s_cnt[0] = 0;
             s_fsel ^= 1;
             s_hi = nhi;
+            s_width = width;
+            s_work = 0;
             if (wall_clock64() - c0 > V.time_limit) s_stop = 1;
         }
         __syncthreads();

@@ -96,8 +96,8 @@ struct ReachView {
     int32_t* cnt;       // members counted so far (exact up to k)
     int64_t* dsum;      // distance sum of the first min(k, cnt) members
     int64_t* tk;        // T once the k-th member is found
-    uint64_t* seen;     // [n][W] bits of this batch at the node
-    uint64_t* nx;       // [n][W] pending bits of this level
+    uint64_t* seen;     // [n][2W] bits of this batch at the node, then (nx) the pending bits of this level
+    uint64_t* nx;       // seen + W: one 128-byte line holds both
     uint64_t* fr;       // [n][W] bits the node passes on next level
     uint16_t* lev;      // [n][64W] level at which each bit arrived (open nodes)
     int32_t* stamp;     // batch that last touched the node
@@ -186,6 +186,11 @@ struct WaveList {
     }
 };
 
+// Bound by lines touched per arc and by the latency of its chain (entry, row,
+// end, words, atomic): a node's seen and pending words share a line, members
+// held are not read in the first batch (none are), and only a lane that set a
+// bit looks at the level mark.  First batch of R-MAT 2^20, k = 100: 3.4 ms in
+// all pushes before that and 512 blocks, 2.2 ms now.
 template <int W>
 __global__ __launch_bounds__(kBlock) void k_rch_push(ReachCtl* ctl, ReachView V) {
     if (ctl->phase != kLevel) return;
@@ -194,6 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_rch_push(ReachCtl* ctl, ReachView V)
     const int32_t gl = ctl->gl;
     const int64_t t0 = ctl->t0;
     const int32_t nwa = ctl->nw;
+    const bool fresh = ctl->batch == 1;
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
     __shared__ int32_t stage[kBlock / 64][kWaveStage];
@@ -211,23 +217,27 @@ __global__ __launch_bounds__(kBlock) void k_rch_push(ReachCtl* ctl, ReachView V)
             int64_t w = 0;
             bool first = false;
             if (a < a1) w = V.col[a];
-            // a node holding more than k earlier members takes no part
-            if (a < a1 && held_before(V, w, t0) <= V.k) {
-                uint64_t any = 0;
+            // a node holding more than k earlier members takes no part (in the
+            // first batch none holds any)
+            if (a < a1 && (fresh || held_before(V, w, t0) <= V.k)) {
+                bool set = false;
 #pragma unroll
                 for (int j = 0; j < W; j++) {
                     if (!f[j]) continue;
-                    const uint64_t b = f[j] & ~V.seen[w * W + j];
+                    const uint64_t b = f[j] & ~V.seen[w * 2 * W + j];
                     if (!b) continue;
-                    any |= b;
                     // only bits not already pending need the atomic, so a popular
                     // target stops taking atomics once it holds the level's bits
                     // (a stale read only lets a redundant atomic through)
                     const uint64_t r =
-                        b & ~__hip_atomic_load(&V.nx[w * W + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (r) atomicOr((unsigned long long*)&V.nx[w * W + j], (unsigned long long)r);
+                        b & ~__hip_atomic_load(&V.nx[w * 2 * W + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (r) {
+                        atomicOr((unsigned long long*)&V.nx[w * 2 * W + j], (unsigned long long)r);
+                        set = true;
+                    }
                 }
-                if (any && V.lmark[w] != gl) first = atomicExch(&V.lmark[w], gl) != gl;
+                // bits found pending were set, and the node queued, by another lane
+                if (set && V.lmark[w] != gl) first = atomicExch(&V.lmark[w], gl) != gl;
             }
             cand.put(first, (int32_t)w);
         }
@@ -262,12 +272,12 @@ __global__ __launch_bounds__(kBlock) void k_rch_merge(ReachCtl* ctl, ReachView V
                 nw[j] = 0;
                 s[j] = 0;
                 if (j >= nwa) continue;
-                const uint64_t p = V.nx[w * W + j];
-                const uint64_t old = V.seen[w * W + j];
+                const uint64_t p = V.nx[w * 2 * W + j];
+                const uint64_t old = V.seen[w * 2 * W + j];
                 nw[j] = p & ~old;
                 s[j] = old | nw[j];
-                if (p) V.nx[w * W + j] = 0;
-                if (nw[j]) V.seen[w * W + j] = s[j];
+                if (p) V.nx[w * 2 * W + j] = 0;
+                if (nw[j]) V.seen[w * 2 * W + j] = s[j];
                 any |= nw[j];
             }
             if (V.stamp[w] != batch) {  // each candidate appears once per level
@@ -351,9 +361,9 @@ __global__ __launch_bounds__(kBlock) void k_rch_merge(ReachCtl* ctl, ReachView V
 // passes over the rest.  Without this nearly every later batch was a round of
 // such sources: R-MAT, 2^20 nodes, k = 100: 51,000 sources with nowhere to go
 // in 100 batches of about 90 us, 8 of 14.7 ms.  A group of eight lanes takes a
-// source and looks at kProbe arcs at most (one past them counts as live).
+// source and looks at kProbe arcs at most (a source with more counts as live).
 constexpr int kWeedGroup = 8;
-constexpr uint32_t kProbe = 512;
+constexpr uint32_t kProbe = 128;
 constexpr int32_t kWeedLeast = 2048;  // listed sources left from which weeding (about 30 us) saves several batches
 
 template <class End>
@@ -367,14 +377,21 @@ __device__ void weed(const ReachCtl* ctl, int32_t k, const uint32_t* rp, End end
     for (int64_t c = first / kActChunk + blockIdx.x; c < nchunks; c += gridDim.x) {
         if (threadIdx.x == 0) count = live = 0;
         __syncthreads();
+        int32_t s[kActPer];
+        bool open[kActPer];
+#pragma unroll
         for (int q = 0; q < kActPer; q++) {
             const int64_t i = c * kActChunk + q * kBlock + threadIdx.x;
-            int32_t s = -1;
-            if (i >= first && i < nact) s = act_src[i];
-            const bool open = s >= 0 && cnt[s] <= k;
-            if (s >= 0 && !open) act_src[i] = -1;
-            const int at = wave_append(&count, open);
-            if (at >= 0) list[at] = q * kBlock + threadIdx.x;
+            s[q] = i >= first && i < nact ? act_src[i] : -1;
+        }
+#pragma unroll
+        for (int q = 0; q < kActPer; q++) open[q] = s[q] >= 0 && cnt[s[q]] <= k;
+#pragma unroll
+        for (int q = 0; q < kActPer; q++) {
+            const int32_t at = q * kBlock + (int32_t)threadIdx.x;
+            if (s[q] >= 0 && !open[q]) act_src[c * kActChunk + at] = -1;
+            const int to = wave_append(&count, open[q]);
+            if (to >= 0) list[to] = at;
         }
         __syncthreads();
         const int32_t total = count;
@@ -522,7 +539,7 @@ __device__ void start_batch(ReachCtl* ctl, const ReachView& V) {
                 if (b == cap - 1) last_idx = i0 + q;
                 V.src_rank[b] = rk[q];
                 V.sbit[x] = b;
-                V.seen[x * W + (b >> 6)] = bit;
+                V.seen[x * 2 * W + (b >> 6)] = bit;
                 V.stamp[x] = batch;
                 V.fr[x * W + (b >> 6)] = bit;
                 V.touched[b] = (int32_t)x;
@@ -600,9 +617,9 @@ __global__ __launch_bounds__(kBlock) void k_rch_account(ReachCtl* ctl, ReachView
         uint64_t s[W];
 #pragma unroll
         for (int j = 0; j < W; j++) {  // fr is a subset of seen: clear both where seen has bits
-            s[j] = j < nwa ? V.seen[w * W + j] : 0ull;
+            s[j] = j < nwa ? V.seen[w * 2 * W + j] : 0ull;
             if (s[j]) {
-                V.seen[w * W + j] = 0;
+                V.seen[w * 2 * W + j] = 0;
                 V.fr[w * W + j] = 0;
             }
         }
@@ -1562,8 +1579,8 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
     V.cnt = (int32_t*)take(sizeof(int32_t) * n);
     V.dsum = (int64_t*)take(sizeof(int64_t) * n);
     V.tk = (int64_t*)take(sizeof(int64_t) * n);
-    V.seen = (uint64_t*)take(sizeof(uint64_t) * n * W);
-    V.nx = (uint64_t*)take(sizeof(uint64_t) * n * W);
+    V.seen = (uint64_t*)take(sizeof(uint64_t) * n * 2 * W);
+    V.nx = V.seen + W;
     V.fr = (uint64_t*)take(sizeof(uint64_t) * n * W);
     V.lev = (uint16_t*)take(sizeof(uint16_t) * n * 64 * W);
     V.stamp = (int32_t*)take(sizeof(int32_t) * n);
@@ -1589,8 +1606,7 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
     fill_u32(st, V.cnt, 0u, (size_t)n);
     fill_u32(st, V.dsum, 0u, (size_t)n * 2);
     fill_u32(st, V.tk, 0u, (size_t)n * 2);
-    fill_u32(st, V.seen, 0u, (size_t)n * W * 2);
-    fill_u32(st, V.nx, 0u, (size_t)n * W * 2);
+    fill_u32(st, V.seen, 0u, (size_t)n * W * 4);
     fill_u32(st, V.fr, 0u, (size_t)n * W * 2);
     fill_u32(st, V.stamp, 0xFFFFFFFFu, (size_t)n);
     fill_u32(st, V.lmark, 0xFFFFFFFFu, (size_t)n);
@@ -1609,7 +1625,7 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
     const int64_t nbatches = (V.nsrc + kFirstBatch - 1) / kFirstBatch + 1;
     const int64_t max_cycles = nbatches * (n + 2);
     int64_t cycles = 0;
-    int32_t chunk = 16;
+    int32_t chunk = 8;
     ReachCtl hc{};
     for (;;) {
         for (int32_t c = 0; c < chunk; c++) {
@@ -1623,7 +1639,8 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
         CCG_HIP(hipStreamSynchronize(st));
         if (hc.phase == kFinished) break;
         if (cycles > max_cycles) throw HipError{hipErrorLaunchTimeOut, "reachability sampling did not finish"};
-        if (chunk < 256) chunk *= 2;
+        // most estimates end within three dozen cycles; an idle one costs three launches
+        if (cycles >= 32 && chunk < 256) chunk *= 2;
     }
     if (weighted)
         hipLaunchKernelGGL(k_rch_out_beta<uint16_t>, dim3(gn), dim3(256), 0, st, V, (const uint16_t*)V.mem_d, a.orig,

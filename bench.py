@@ -371,7 +371,8 @@ def reach_bench(args, graphgen, cc, torch):
 
 def wsearch_roofline(timings, workload: str, n: int, arcs: int, k: int, tuning: dict) -> dict:
     """Per-launch algorithmic bytes / average launch duration of the weighted
-    searches' kernel (one launch of one workgroup per sample).  Algorithmic
+    searches' kernel (one launch of one workgroup per sample, or rounds over
+    patches on graphs that can be cut into them).  Algorithmic
     bytes are those of a label-setting search that takes every node once and
     relaxes every arc once: 16 B per node (its distance word and its two row
     bounds) and 16 B per arc (its packed end and length, and the far end's
@@ -383,6 +384,13 @@ def wsearch_roofline(timings, workload: str, n: int, arcs: int, k: int, tuning: 
     if launches == 0 or ms <= 0:
         return {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
                 "traffic": None, "kernel": "k_wsearch"}
+    if launches > len(timings):  # searched by patches: rounds of launches, relaxations in LDS and not counted
+        per = 16 * k * (n + arcs) * len(timings) / launches
+        achieved = per / (ms / launches / 1e3) / 1e9
+        return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None, "kernel": "k_patch_round",
+                "algorithmic_bytes_per_launch": int(per), "avg_launch_us": round(ms / launches * 1e3, 1),
+                "launches_per_step": round(launches / len(timings), 1), "bytes_per_node_and_arc": 16}
     per = 16 * k * (n + arcs) * len(timings) / launches
     achieved = per / (ms / launches / 1e3) / 1e9
     relaxed = sum(t["arcs_scanned"] for t in timings) / len(timings)

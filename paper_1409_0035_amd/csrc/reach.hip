@@ -96,8 +96,8 @@ struct ReachView {
     int32_t* cnt;       // members counted so far (exact up to k)
     int64_t* dsum;      // distance sum of the first min(k, cnt) members
     int64_t* tk;        // T once the k-th member is found
-    uint64_t* seen;     // [n][2W] bits of this batch at the node, then (nx) the pending bits of this level
-    uint64_t* nx;       // seen + W: one 128-byte line holds both
+    uint64_t* seen;     // [n][W][2] bits of this batch at the node, each word followed by
+    uint64_t* nx;       // the pending bits of this level (seen + 1), so that one line holds both
     uint64_t* fr;       // [n][W] bits the node passes on next level
     uint16_t* lev;      // [n][64W] level at which each bit arrived (open nodes)
     int32_t* stamp;     // batch that last touched the node
@@ -224,15 +224,15 @@ __global__ __launch_bounds__(kBlock) void k_rch_push(ReachCtl* ctl, ReachView V)
 #pragma unroll
                 for (int j = 0; j < W; j++) {
                     if (!f[j]) continue;
-                    const uint64_t b = f[j] & ~V.seen[w * 2 * W + j];
+                    const uint64_t b = f[j] & ~V.seen[w * 2 * W + 2 * j];
                     if (!b) continue;
                     // only bits not already pending need the atomic, so a popular
                     // target stops taking atomics once it holds the level's bits
                     // (a stale read only lets a redundant atomic through)
                     const uint64_t r =
-                        b & ~__hip_atomic_load(&V.nx[w * 2 * W + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        b & ~__hip_atomic_load(&V.nx[w * 2 * W + 2 * j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (r) {
-                        atomicOr((unsigned long long*)&V.nx[w * 2 * W + j], (unsigned long long)r);
+                        atomicOr((unsigned long long*)&V.nx[w * 2 * W + 2 * j], (unsigned long long)r);
                         set = true;
                     }
                 }
@@ -272,12 +272,12 @@ __global__ __launch_bounds__(kBlock) void k_rch_merge(ReachCtl* ctl, ReachView V
                 nw[j] = 0;
                 s[j] = 0;
                 if (j >= nwa) continue;
-                const uint64_t p = V.nx[w * 2 * W + j];
-                const uint64_t old = V.seen[w * 2 * W + j];
+                const uint64_t p = V.nx[w * 2 * W + 2 * j];
+                const uint64_t old = V.seen[w * 2 * W + 2 * j];
                 nw[j] = p & ~old;
                 s[j] = old | nw[j];
-                if (p) V.nx[w * 2 * W + j] = 0;
-                if (nw[j]) V.seen[w * 2 * W + j] = s[j];
+                if (p) V.nx[w * 2 * W + 2 * j] = 0;
+                if (nw[j]) V.seen[w * 2 * W + 2 * j] = s[j];
                 any |= nw[j];
             }
             if (V.stamp[w] != batch) {  // each candidate appears once per level
@@ -539,7 +539,7 @@ __device__ void start_batch(ReachCtl* ctl, const ReachView& V) {
                 if (b == cap - 1) last_idx = i0 + q;
                 V.src_rank[b] = rk[q];
                 V.sbit[x] = b;
-                V.seen[x * 2 * W + (b >> 6)] = bit;
+                V.seen[x * 2 * W + 2 * (b >> 6)] = bit;
                 V.stamp[x] = batch;
                 V.fr[x * W + (b >> 6)] = bit;
                 V.touched[b] = (int32_t)x;
@@ -617,9 +617,9 @@ __global__ __launch_bounds__(kBlock) void k_rch_account(ReachCtl* ctl, ReachView
         uint64_t s[W];
 #pragma unroll
         for (int j = 0; j < W; j++) {  // fr is a subset of seen: clear both where seen has bits
-            s[j] = j < nwa ? V.seen[w * 2 * W + j] : 0ull;
+            s[j] = j < nwa ? V.seen[w * 2 * W + 2 * j] : 0ull;
             if (s[j]) {
-                V.seen[w * 2 * W + j] = 0;
+                V.seen[w * 2 * W + 2 * j] = 0;
                 V.fr[w * W + j] = 0;
             }
         }
@@ -1580,7 +1580,7 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
     V.dsum = (int64_t*)take(sizeof(int64_t) * n);
     V.tk = (int64_t*)take(sizeof(int64_t) * n);
     V.seen = (uint64_t*)take(sizeof(uint64_t) * n * 2 * W);
-    V.nx = V.seen + W;
+    V.nx = V.seen + 1;
     V.fr = (uint64_t*)take(sizeof(uint64_t) * n * W);
     V.lev = (uint16_t*)take(sizeof(uint16_t) * n * 64 * W);
     V.stamp = (int32_t*)take(sizeof(int32_t) * n);

@@ -379,12 +379,13 @@ def wsearch_roofline(timings, workload: str, n: int, arcs: int, k: int, tuning: 
     8-byte word), k (n + arcs) x 16 per launch on a connected graph.  The
     device's own counts of nodes taken and arcs relaxed give the re-work of
     the Delta-stepping phases beside it."""
+    from paper_1409_0035_amd import CC_SEARCH_PATCHES
     launches = sum(t["kernel_launches"] for t in timings)
     ms = sum(t["kernel_ms"] for t in timings)
     if launches == 0 or ms <= 0:
         return {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
                 "traffic": None, "kernel": "k_wsearch"}
-    if launches > len(timings):  # searched by patches: rounds of launches, relaxations in LDS and not counted
+    if all(t["search"] == CC_SEARCH_PATCHES for t in timings):  # rounds of launches, relaxations in LDS and not counted
         per = 16 * k * (n + arcs) * len(timings) / launches
         achieved = per / (ms / launches / 1e3) / 1e9
         return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -484,7 +485,7 @@ def run_config(name, cc, graphgen, torch, steps, warmup, plain_steps, autotune=T
     wall = time.perf_counter() - t_start
     ms_per_step = wall * 1e3 / steps
     gteps = edges / (ms_per_step / 1e3) / 1e9
-    replayed = sum(1 for t in timings if t["launches"] == 1)
+    replayed = sum(1 for t in timings if t["search"] & cc.CC_SEARCH_REPLAY)
     log(f"  batched{' (graph replays: %d)' % replayed if use_graph else ''}: {ms_per_step:.3f} ms/step, "
         f"{gteps:.1f} GTEPS")
     if use_graph:  # replays carry no per-launch timing: take it from eager steps

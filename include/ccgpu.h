@@ -233,6 +233,14 @@ cc_status cc_estimate_device_noalloc(cc_context* ctx, const cc_graph* g, const c
 cc_status cc_estimate_batch(cc_context* ctx, int32_t count, const cc_graph* const* graphs, const cc_params* params,
                             cc_result* outs, cc_status* statuses);
 
+/* Which search an estimate ran (cc_timing.search) */
+#define CC_SEARCH_LEVELS 1   /* bit-parallel levels (CC_BATCHED, unit lengths) */
+#define CC_SEARCH_SMALL 2    /* one workgroup per sample (small graphs) */
+#define CC_SEARCH_PLAIN 3    /* one sample at a time (CC_PLAIN) */
+#define CC_SEARCH_WEIGHTED 4 /* arc lengths: delta-stepping, one workgroup per sample */
+#define CC_SEARCH_PATCHES 5  /* arc lengths: patch by patch in LDS */
+#define CC_SEARCH_REPLAY 0x100
+
 /* Timing of the last cc_estimate / cc_estimate_device on this context, from
  * HIP events recorded on the stream the kernels ran on (milliseconds; small
  * graphs: from the device's clock read by the kernels), plus
@@ -244,9 +252,11 @@ typedef struct {
     int64_t levels;        /* BFS levels / delta-stepping phases executed */
     int64_t arcs_scanned;  /* adjacency entries read by the traversal kernels */
     int64_t nodes_visited; /* node-level work items processed by the traversal */
-    int64_t launches;      /* all traversal launches (including bookkeeping kernels) */
+    int64_t launches;      /* all traversal launches (including bookkeeping kernels); 1 for a replay, and for a
+                              small graph's search, which is one launch (see `search`) */
     int32_t dist_bytes;    /* bytes per stored distance (1, 2 or 4) */
-    int32_t reserved;
+    int32_t search;        /* the search that ran: CC_SEARCH_..., with CC_SEARCH_REPLAY or-ed in when the call
+                              replayed a captured graph; 0 when the call searches otherwise (reachability) */
     double kernel_ms;      /* summed duration of the level batches (device time from first to last level) */
     int64_t kernel_launches; /* levels enqueued */
     int64_t arcs_matched;  /* arcs pushed along by push levels */

@@ -25,6 +25,9 @@ CC_EDEVICE, CC_EBUSY, CC_ECANCELLED, CC_ENOTREADY = 5, 6, 7, 8
 CC_DIRECTED, CC_VALIDATE = 1, 2
 CC_BATCHED, CC_PLAIN = 0, 1
 CC_GRAPH = 0x100  # or-ed into CC_BATCHED: capture the estimate as a HIP graph and replay it
+# the search an estimate ran (cc_last_timing()["search"])
+CC_SEARCH_LEVELS, CC_SEARCH_SMALL, CC_SEARCH_PLAIN, CC_SEARCH_WEIGHTED, CC_SEARCH_PATCHES = range(1, 6)
+CC_SEARCH_REPLAY = 0x100  # or-ed in: a captured graph was replayed
 
 EXPORTED = [
     "cc_context_create", "cc_context_destroy", "cc_graph_upload", "cc_graph_borrow_device", "cc_graph_release",
@@ -92,7 +95,7 @@ class cc_timing(ctypes.Structure):
     _fields_ = [("total_ms", ctypes.c_double), ("traverse_ms", ctypes.c_double),
                 ("epilogue_ms", ctypes.c_double), ("levels", ctypes.c_int64), ("arcs_scanned", ctypes.c_int64),
                 ("nodes_visited", ctypes.c_int64), ("launches", ctypes.c_int64), ("dist_bytes", ctypes.c_int32),
-                ("reserved", ctypes.c_int32), ("kernel_ms", ctypes.c_double), ("kernel_launches", ctypes.c_int64),
+                ("search", ctypes.c_int32), ("kernel_ms", ctypes.c_double), ("kernel_launches", ctypes.c_int64),
                 ("arcs_matched", ctypes.c_int64), ("scatter_ms", ctypes.c_double),
                 ("scatter_launches", ctypes.c_int64), ("scatter_arcs", ctypes.c_int64), ("hub_arcs", ctypes.c_int64),
                 ("pull_scatter_ms", ctypes.c_double), ("pull_levels", ctypes.c_int64)]

@@ -394,6 +394,7 @@ struct Lane {
         int32_t lmax = 0, levels = 0;
         int32_t lmax_fwd = -1, levels_fwd = 0;  // round trip: the forward search (the reverse one above)
         bool weighted = false;  // weighted searches: lmax_fwd, lmax bound each direction's largest distance
+        int32_t search = 0;     // CC_SEARCH_...
     };
     std::vector<Captured> captured;  // most recently used last
     static constexpr size_t kMaxCaptured = 8;
@@ -1325,7 +1326,7 @@ size_t job_bytes(const DevGraph& g, int32_t k, int32_t mode, int db) {
     return b;
 }
 
-void record_timing(cc_timing* timing, Lane& L, const TravStats& stats, int db) {
+void record_timing(cc_timing* timing, Lane& L, const TravStats& stats, int db, int32_t search) {
     if (!timing) return;
     timing->traverse_ms = elapsed(L.ev[0], L.ev[1]);
     timing->epilogue_ms = elapsed(L.ev[1], L.ev[2]);
@@ -1335,6 +1336,7 @@ void record_timing(cc_timing* timing, Lane& L, const TravStats& stats, int db) {
     timing->nodes_visited = stats.nodes_visited;
     timing->launches = stats.launches;
     timing->dist_bytes = db;
+    timing->search = search;
     timing->kernel_ms = stats.kernel_ms;
     timing->kernel_launches = stats.kernel_launches;
     timing->arcs_matched = stats.push_arcs;
@@ -1541,6 +1543,7 @@ bool run_small(cc_context* ctx, const cc_graph* gr, const Resolved& r, const std
         timing->nodes_visited = (int64_t)n * k;
         timing->launches = timing->kernel_launches = 1;
         timing->dist_bytes = 1;
+        timing->search = CC_SEARCH_SMALL;
     }
     *result = finish_flags(hf);
     return true;
@@ -1726,6 +1729,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                             *timing = cc_timing{};
                             timing->total_ms = timing->traverse_ms = elapsed(L.ev[0], L.ev[2]);
                             timing->launches = 1;
+                            timing->search = cap_e->search | CC_SEARCH_REPLAY;
                         }
                         return CC_OK;
                     }
@@ -1745,6 +1749,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                         timing->arcs_scanned = hc.arcs;
                         timing->nodes_visited = hc.nodes;
                         timing->launches = 1;
+                        timing->search = cap_e->search | CC_SEARCH_REPLAY;
                         timing->pull_levels = hc.pull_levels;
                     }
                     return CC_OK;
@@ -1970,7 +1975,11 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
         CCG_HIP(hipEventRecord(L.ev[2], st));
         CCG_HIP(hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, st));
         CCG_HIP(hipStreamSynchronize(st));
-        record_timing(timing, L, stats, bits_path ? 0 : (int)dk);
+        const int32_t search = mode == CC_PLAIN ? CC_SEARCH_PLAIN
+                               : !g.weighted    ? CC_SEARCH_LEVELS
+                               : patched        ? CC_SEARCH_PATCHES
+                                                : CC_SEARCH_WEIGHTED;
+        record_timing(timing, L, stats, bits_path ? 0 : (int)dk, search);
         if (timing) timing->levels = stats.levels;
         const cc_status fs = finish_flags(hf);
         if (want_graph && fs == CC_OK && (stats.bfs_levels > 0 || w_single)) {
@@ -1978,6 +1987,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
             // the epilogue for its deepest level) for replay; nothing runs now
             Lane::Captured cap_e;
             cap_e.key = graph_key();
+            cap_e.search = search;
             cap_e.lmax = bits_path ? ba.lmax : lmax_dir[1];
             cap_e.levels = bits_path ? stats.bfs_levels : levels_dir[1];
             if (rt_single) {
@@ -2542,7 +2552,7 @@ cc_status run_batch(cc_context* ctx, std::vector<BatchItem>& items, Lane& L, cc_
         DevFlags hf;
         CCG_HIP(hipMemcpyAsync(&hf, flags, sizeof(hf), hipMemcpyDeviceToHost, st));
         CCG_HIP(hipStreamSynchronize(st));
-        record_timing(timing, L, stats, 0);
+        record_timing(timing, L, stats, 0, CC_SEARCH_LEVELS);
         return finish_flags(hf);
     }
     return fail(CC_EDEVICE, "batch traversal did not settle");

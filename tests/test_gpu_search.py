@@ -1,0 +1,41 @@
+"""cc_last_timing says which search an estimate ran and whether it replayed a
+captured graph: a small graph's one launch is no replay."""
+import numpy as np
+import pytest
+
+import graphgen
+import paper_1409_0035_amd as cc
+
+pytestmark = pytest.mark.gpu
+
+
+def _searches(ctx, gh, n, k, modes, samples):
+    import torch
+    out = {"S_hyb": torch.empty(n, dtype=torch.float64, device="cuda")}
+    got = []
+    for mode in modes:
+        cc.cc_estimate_device(ctx.handle, gh, k, out, mode=mode, samples=samples)
+        got.append(cc.cc_last_timing(ctx.handle)["search"])
+    return got
+
+
+GRAPH = cc.CC_BATCHED | cc.CC_GRAPH
+CASES = {
+    "small": (lambda: graphgen.ba(2000, 4, seed=1), cc.CC_SEARCH_SMALL, False),
+    "past-the-small": (lambda: graphgen.ba(49153, 4, seed=1), cc.CC_SEARCH_LEVELS, True),
+    "patches": (lambda: graphgen.grid(30, 40, 8, 0.1, 1, 1000, seed=1), cc.CC_SEARCH_PATCHES, True),
+    "weighted": (lambda: graphgen.with_lengths(graphgen.ba(3000, 4, seed=1), 1, 50, 2), cc.CC_SEARCH_WEIGHTED, True),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_search_is_named(name):
+    make, search, replays = CASES[name]
+    g = make()
+    samples = np.arange(5, 25, dtype=np.int32)
+    with cc.Context(0) as ctx:
+        gh = ctx.upload(g)
+        got = _searches(ctx, gh, g.n, 20, (cc.CC_BATCHED, GRAPH, GRAPH, cc.CC_PLAIN), samples)
+        again = search | (cc.CC_SEARCH_REPLAY if replays else 0)
+        assert got == [search, search, again, cc.CC_SEARCH_PLAIN]
+        ctx.release(gh)

@@ -39,3 +39,28 @@ def test_search_is_named(name):
         again = search | (cc.CC_SEARCH_REPLAY if replays else 0)
         assert got == [search, search, again, cc.CC_SEARCH_PLAIN]
         ctx.release(gh)
+
+
+def test_small_graph_time_includes_its_error_pass():
+    """total_ms runs to the last output: with the Sec. 4 outputs and the sweep
+    asked for, the epilogue of a small graph counts them (they take several
+    times what the estimates do)."""
+    import torch
+    g = graphgen.ba(20000, 4, seed=2)
+    k = 256
+    est = {"S_hyb": torch.empty(g.n, dtype=torch.float64, device="cuda")}
+    both = {**est, **{f: torch.empty(g.n, dtype=torch.float64, device="cuda")
+                      for f in ("S_err", "S_ad", "S_ad_err", "S_sweep", "S_sweep_err")}}
+    with cc.Context(0) as ctx:
+        gh = ctx.upload(g)
+        ms = []
+        for out in (est, both):
+            for _ in range(3):
+                cc.cc_estimate_device(ctx.handle, gh, k, out, seed=1)
+            t = cc.cc_last_timing(ctx.handle)
+            assert t["search"] == cc.CC_SEARCH_SMALL
+            assert abs(t["total_ms"] - t["traverse_ms"] - t["epilogue_ms"]) < 1e-9
+            ms.append(t["epilogue_ms"])
+        print(f"  epilogue {ms[0]:.4f} ms, with errors {ms[1]:.4f} ms")
+        assert ms[1] > 2 * ms[0]
+        ctx.release(gh)

@@ -478,7 +478,8 @@ __global__ __launch_bounds__(kSB) void k_small_search(SmallArgs a, SmallSamples 
     }
     scanned = wave_sum64(scanned);
     __syncthreads();
-    if (lane == 0) S.part[wave] = (uint32_t)min(scanned, (int64_t)(INT32_MAX / kSWaves));
+    // a level reads an arc once at most: 2 x 254 levels of 2^21 arcs fit 32 bits
+    if (lane == 0) S.part[wave] = (uint32_t)scanned;
     __syncthreads();
     if (tid == 0) {
         uint32_t s = 0;

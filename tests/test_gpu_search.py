@@ -64,3 +64,30 @@ def test_small_graph_time_includes_its_error_pass():
         print(f"  epilogue {ms[0]:.4f} ms, with errors {ms[1]:.4f} ms")
         assert ms[1] > 2 * ms[0]
         ctx.release(gh)
+
+
+def test_arcs_scanned_is_not_clipped():
+    """A chain of 236 nodes with 2,100 parallel arcs between neighbours, and at
+    its end two nodes joined by 500,000: the levels pull, and one wave reads
+    the two long rows again in each of them until the search arrives, past
+    2^31 / 16 arcs."""
+    chain, thick, long_row = 236, 2100, 500_000
+    a, b = chain, chain + 1
+    i = np.arange(chain - 1)
+    src = np.concatenate([np.repeat(i, thick), [chain - 1], np.full(long_row, a)])
+    dst = np.concatenate([np.repeat(i + 1, thick), [a], np.full(long_row, b)])
+    s, d = np.concatenate([src, dst]), np.concatenate([dst, src])
+    order = np.argsort(s, kind="stable")
+    n = chain + 2
+    rp = np.zeros(n + 1, dtype=np.int64)
+    rp[1:] = np.cumsum(np.bincount(s, minlength=n))
+    assert s.size <= 1 << 21
+    with cc.Context(0) as ctx:
+        gh = cc.cc_graph_upload(ctx.handle, n, s.size, rp, d[order].astype(np.int32))
+        res = cc.cc_estimate(ctx.handle, gh, 1, samples=[0], outputs=("src_sum",))
+        t = cc.cc_last_timing(ctx.handle)
+        print(f"  arcs scanned {t['arcs_scanned']}, {t['total_ms']:.1f} ms")
+        assert t["search"] == cc.CC_SEARCH_SMALL and res["src_sum"][0] == n * (n - 1) // 2
+        # every level from the tenth on pulls, and reads the rows of all nodes not yet found
+        assert t["arcs_scanned"] > sum(2 * long_row + 2 * thick * (chain - level) for level in range(10, chain - 1))
+        cc.cc_graph_release(gh)

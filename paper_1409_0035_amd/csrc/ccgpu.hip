@@ -3065,7 +3065,7 @@ extern "C" cc_status cc_autotune(cc_context* ctx, cc_graph* g, int32_t k, uint64
                 for (double f : {0.5, 1.5, 2.0, 3.0, 4.0, 8.0})
                     ds.push_back((int32_t)std::max<double>(1.0, std::llround(d0 * f)));
                 try_knob(&cc_tuning::delta, ds);
-            } else {
+            } else if (!small_search_fits(g, r)) {  // a small graph's search reads none of the knobs
                 try_knob(&cc_tuning::alpha, {1, 2, 8, 16, 32, 64});
                 try_knob(&cc_tuning::scatter_blocks, {2048, 4096, 8192, 16384});
                 try_knob(&cc_tuning::level_blocks, {512, 1024, 2048, 4096});

@@ -91,3 +91,29 @@ def test_arcs_scanned_is_not_clipped():
         # every level from the tenth on pulls, and reads the rows of all nodes not yet found
         assert t["arcs_scanned"] > sum(2 * long_row + 2 * thick * (chain - level) for level in range(10, chain - 1))
         cc.cc_graph_release(gh)
+
+
+def test_autotune_times_a_small_graphs_setting_only():
+    """No knob is read by a small graph's search: the tuner keeps the setting
+    and takes the time of two rounds of estimates (a warm-up and the timed
+    one) instead of measuring its dozen candidates."""
+    import time
+    import torch
+    reps = 100
+    with cc.Context(0) as ctx:
+        g = graphgen.ba(5000, 4, seed=1)
+        gh = ctx.upload(g)
+        out = {"S_hyb": torch.empty(g.n, dtype=torch.float64, device="cuda")}
+        before = cc.cc_graph_get_tuning(gh)
+        for _ in range(2):
+            t0 = time.perf_counter()
+            for _ in range(reps):
+                cc.cc_estimate_device(ctx.handle, gh, 64, out, seed=1)
+            one_round = time.perf_counter() - t0
+        t0 = time.perf_counter()
+        best, ms = cc.cc_autotune(ctx.handle, gh, 64, seed=1, reps=reps)
+        took = time.perf_counter() - t0
+        print(f"  {reps} estimates {one_round * 1e3:.2f} ms, the tuner {took * 1e3:.2f} ms")
+        assert ms > 0 and best == before and cc.cc_graph_get_tuning(gh) == before
+        assert took < 6 * one_round
+        ctx.release(gh)

@@ -629,9 +629,10 @@ size_t small_lds(int32_t npad, int32_t qcap) {
 
 template <bool RT, bool LA>
 void launch_search(hipStream_t st, const SmallArgs& a, const SmallSamples& ss, size_t lds) {
+    // the limit is the kernel's, for all threads: every call sets the same value
     if (lds > 65536)
         CCG_HIP(hipFuncSetAttribute((const void*)k_small_search<RT, LA>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds));
+                                    (int)kLdsBytes));
     hipLaunchKernelGGL((k_small_search<RT, LA>), dim3((unsigned)a.k), dim3(kSB), lds, st, a, ss);
 }
 

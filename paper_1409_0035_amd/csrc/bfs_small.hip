@@ -107,7 +107,8 @@ __device__ __forceinline__ int32_t small_bfs(const Arcs& in, const Arcs& out, in
         S.hist[0] = 1;
     }
     int32_t visited = 1;
-    uint32_t seen = 0;  // arcs visited by this thread
+    uint32_t seen = 0;   // arcs visited by this thread
+    uint32_t known = 0;  // arcs of the nodes found so far, but for levels longer than their list
     const int32_t nchunks = npad / 64;
     for (int32_t level = 1;; level++) {
         const int cur = (level - 1) & 1, nxt = level & 1;
@@ -164,9 +165,17 @@ __device__ __forceinline__ int32_t small_bfs(const Arcs& in, const Arcs& out, in
             __syncthreads();
         }
         // push while the frontier's arcs are few against what a pull would
-        // scan (about one trip of four arcs for each node left), or so few
-        // that a trip or two of the workgroup covers them
-        const bool push = nf <= qcap && (mf <= 4 * kSB || mf < (uint32_t)(n - visited));
+        // scan, or so few that a trip or two of the workgroup covers them.  A
+        // pull reads a node's arcs until one ends at a node found before: about
+        // arcs / known of them where arcs end anywhere, but no more than the
+        // node has (arcs / n), and four at the least.  (A pull taken for one
+        // trip of four arcs a node, which holds where hubs were found early,
+        // read most of a flat random graph's arcs in its widest level: 49,000
+        // nodes of 40 arcs, 64 samples 339 -> 193 us; R-MAT scale 16 217 ->
+        // 177 us.)
+        known += mf;
+        const float four = 4.0f * (float)max((uint32_t)n, known);
+        const bool push = nf <= qcap && (mf <= 4 * kSB || (float)mf * four < (float)(n - visited) * fmaxf((float)out.arcs, four));
         if (push) {
             int32_t top = 1;
             while (top < nf) top <<= 1;

@@ -546,11 +546,17 @@ constexpr int32_t kSmallT = 256;       // entries of a sample's tail tables: dis
 constexpr int32_t kSmallStamps = 64;
 // The graphs searched that way: one distance byte a node, the visited bits and
 // the frontier fit LDS up to 65,536 nodes; the line lies lower, where the
-// bit-parallel search's replays draw level (k = 64, replays against this
-// path's calls: preferential attachment 20,000 nodes 193 against 104 us,
-// 40,000 nodes 210 / 176, 65,536 nodes 224 / 252; R-MAT scale 15 189 / 126,
-// scale 16 (47,000 nodes, 1.9 M arcs) 220 / 208; round trips on directed R-MAT
-// scale 15 329 / 169, scale 16 356 / 266, scale 17 (55,000 nodes) 345 / 472).
+// bit-parallel search's replays draw level (us, k = 64, replays against this
+// path's calls: preferential attachment 20,000 nodes 183 against 95, 40,000
+// nodes 210 / 176, 65,536 nodes 224 / 252; R-MAT scale 15 194 / 103, scale 16
+// (47,000 nodes, 1.8 M arcs) 205 / 174; round trips on directed R-MAT scale 15
+// 329 / 139, scale 16 356 / 231, scale 17 (55,000 nodes) 345 / 472).  Graphs
+// without hubs draw level earlier: random graphs of 20,000 nodes and 40 arcs a
+// node 180 / 133, of 49,000 nodes 197 / 213 with 8 arcs, 160 / 225 with 16 and
+// 195 / 190 with 40; a star of 49,000 nodes 90 / 112.  But a replay holds only
+// while other samples' searches have the captured depth, and costs 550 to 950
+// there when it does not; eager estimates took 305 to 450.  (With 16 and 256
+// samples instead of 64 the sums over these graphs stand alike.)
 constexpr int64_t kSmallNodes = 49152;
 constexpr int64_t kSmallArcs = (int64_t)1 << 21;
 // What a search reports, in pinned host memory.

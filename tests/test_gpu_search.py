@@ -117,3 +117,21 @@ def test_autotune_times_a_small_graphs_setting_only():
         assert ms > 0 and best == before and cc.cc_graph_get_tuning(gh) == before
         assert took < 6 * one_round
         ctx.release(gh)
+
+
+def test_flat_graph_is_pushed_until_pulls_end_early():
+    """A random graph without hubs: at its third level some 1,600 of 49,000 nodes
+    are known, so that a pull would read most of the arcs, and the search still
+    pushes (their 64,000 arcs)."""
+    n, deg, k = 49000, 40, 16
+    r = np.random.default_rng(4)
+    g = graphgen.csr_from_arcs(n, r.integers(0, n, n * deg // 2), r.integers(0, n, n * deg // 2))
+    with cc.Context(0) as ctx:
+        gh = ctx.upload(g)
+        cc.cc_estimate(ctx.handle, gh, k, seed=1, outputs=("S_hyb",))
+        t = cc.cc_last_timing(ctx.handle)
+        print(f"  {t['arcs_scanned'] / k / g.arcs:.3f} of {g.arcs} arcs a search")
+        assert t["search"] == cc.CC_SEARCH_SMALL
+        # the pushes, and pulls with more than half of the nodes known (two arcs a node and a trip's rest)
+        assert t["arcs_scanned"] < k * g.arcs / 4
+        ctx.release(gh)

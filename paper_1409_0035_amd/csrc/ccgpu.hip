@@ -836,6 +836,143 @@ static void zip_weighted(cc_graph* g, int a, int b, hipStream_t st) {
     CCG_HIP(hipStreamSynchronize(st));
 }
 
+// Puts a graph on the device with its nodes in the order `orig` (and, unless
+// pstart is empty, cut into those patches): relabelled arcs of both directions,
+// hub chunks, id maps, patch tables.  False when the patches cannot serve (one
+// has too many neighbours).
+static bool place_graph(cc_graph* g, const int64_t* row_ptr, const int32_t* col_idx, const int32_t* w,
+                        const std::vector<int32_t>& orig, const std::vector<int32_t>& pstart) {
+    const int64_t n = g->dg.n, arcs = g->dg.arcs;
+    const bool directed = g->dg.directed;
+    g->inv.assign((size_t)n, 0);
+    for (int64_t i = 0; i < n; i++) g->inv[(size_t)orig[(size_t)i]] = (int32_t)i;
+    // ---- relabelled out-arcs
+    std::vector<uint32_t> rp((size_t)n + 1, 0);
+    std::vector<int32_t> col((size_t)arcs), ww(w ? (size_t)arcs : 0);
+    for (int64_t i = 0; i < n; i++) {
+        const int64_t v = orig[(size_t)i];
+        rp[(size_t)i + 1] = rp[(size_t)i] + (uint32_t)(row_ptr[v + 1] - row_ptr[v]);
+    }
+    parallel_ranges(0, n, [&](int64_t i0, int64_t i1) {
+        for (int64_t i = i0; i < i1; i++) {
+            const int64_t v = orig[(size_t)i];
+            uint32_t q = rp[(size_t)i];
+            for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; e++, q++) {
+                col[q] = g->inv[(size_t)col_idx[e]];
+                if (w) ww[q] = w[e];
+            }
+            // rows in id order: a chunk's lanes then read neighbouring masks
+            if (!w) std::sort(col.begin() + rp[(size_t)i], col.begin() + rp[(size_t)i + 1]);
+        }
+    });
+    std::vector<uint32_t> trp;
+    std::vector<int32_t> tcol, tw;
+    if (directed) transpose_host(n, rp, col, ww, trp, tcol, tw);
+    // ---- hub prefix (by in-degree of the pull direction; for digraphs by
+    //      the larger of the two, ids being sorted by total degree)
+    const std::vector<uint32_t>& prp = directed ? trp : rp;
+    int64_t hubs = 0;
+    for (int64_t i = 0; i < n; i++) {
+        const uint32_t din = prp[(size_t)i + 1] - prp[(size_t)i];
+        const uint32_t dout = rp[(size_t)i + 1] - rp[(size_t)i];
+        if (std::max(din, dout) > hub_degree(directed)) hubs = i + 1;
+    }
+    int64_t nh = (hubs + 63) / 64 * 64;
+    if (nh > n) nh = n;
+    if (w) nh = 0;
+    g->dg.nh = nh;
+    if (w) {
+        double sw = 0;
+        for (int64_t e = 0; e < arcs; e++) sw += w[e];
+        const double mean = arcs > 0 ? sw / (double)arcs : 1.0;
+        g->dg.delta = (uint32_t)std::max<double>(1.0, std::llround(1.5 * mean));
+    }
+    g->tune.delta = (int32_t)std::min<uint32_t>(std::max<uint32_t>(g->dg.delta, 1u), INT32_MAX);
+    std::vector<int32_t> ch_in = hub_chunk_list(prp, nh, hub_chunk(directed));
+    std::vector<int32_t> ch_out = directed ? hub_chunk_list(rp, nh, hub_chunk(directed)) : std::vector<int32_t>();
+    if (!directed) g->chunks_host = ch_in;
+
+    auto up = [&](int slot, const void* src, size_t bytes) -> void* {
+        void* d = nullptr;
+        hipError_t e = hipMalloc(&d, bytes ? bytes : 4);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            throw std::bad_alloc();
+        }
+        g->mem[slot] = d;
+        g->bytes += bytes;
+        if (bytes) CCG_HIP(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
+        return d;
+    };
+    g->dg.rp = (const uint32_t*)up(0, rp.data(), sizeof(uint32_t) * (n + 1));
+    g->dg.col = (const int32_t*)up(1, col.data(), sizeof(int32_t) * arcs);
+    if (w) g->dg.w = (const int32_t*)up(2, ww.data(), sizeof(int32_t) * arcs);
+    if (directed) {
+        g->dg.rrp = (const uint32_t*)up(3, trp.data(), sizeof(uint32_t) * (n + 1));
+        g->dg.rcol = (const int32_t*)up(4, tcol.data(), sizeof(int32_t) * arcs);
+        if (w) g->dg.rw = (const int32_t*)up(5, tw.data(), sizeof(int32_t) * arcs);
+    } else {
+        g->dg.rrp = g->dg.rp;
+        g->dg.rcol = g->dg.col;
+        g->dg.rw = g->dg.w;
+    }
+    g->dg.orig = (const int32_t*)up(6, orig.data(), sizeof(int32_t) * n);
+    g->dg.inv = (const int32_t*)up(9, g->inv.data(), sizeof(int32_t) * n);
+    g->dg.hub_chunks_in = (const int32_t*)up(7, ch_in.data(), sizeof(int32_t) * ch_in.size());
+    g->dg.n_hub_chunks_in = (int32_t)(ch_in.size() / 3);
+    if (directed) {
+        g->dg.hub_chunks_out = (const int32_t*)up(8, ch_out.data(), sizeof(int32_t) * ch_out.size());
+        g->dg.n_hub_chunks_out = (int32_t)(ch_out.size() / 3);
+    } else {
+        g->dg.hub_chunks_out = g->dg.hub_chunks_in;
+        g->dg.n_hub_chunks_out = g->dg.n_hub_chunks_in;
+    }
+    if (w) zip_weighted(g, 10, 11, nullptr);
+    if (pstart.empty()) return true;
+    PatchGraph& pg = g->dg.patches;
+    int slot = 14;
+    PatchMemory mem;
+    mem.take = [&](size_t bytes) -> void* {
+        void* d = nullptr;
+        if (hipMalloc(&d, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            throw std::bad_alloc();
+        }
+        g->mem[slot++] = d;
+        g->bytes += bytes;
+        return d;
+    };
+    mem.drop = [&](void* d, size_t bytes) {
+        for (void*& p : g->mem)
+            if (p == d) p = nullptr;
+        g->bytes -= bytes;
+        CCG_HIP(hipFree(d));
+    };
+    pg.npatch = (int32_t)pstart.size() - 1;
+    pg.pstart = (const int32_t*)up(12, pstart.data(), sizeof(int32_t) * pstart.size());
+    int32_t* of = (int32_t*)mem.take(sizeof(int32_t) * (size_t)n);
+    pg.patch_of = of;
+    build_patch_of(nullptr, pg.npatch, pg.pstart, of);
+    if (!build_patch_arcs(nullptr, pg, 0, g->dg.rp, g->dg.cw, mem)) return false;
+    if (!directed) pg.dir[1] = pg.dir[0];
+    return !directed || build_patch_arcs(nullptr, pg, 1, g->dg.rrp, g->dg.rcw, mem);
+}
+
+// What place_graph put on the device, given back.
+static void drop_graph(cc_graph* g) {
+    for (void*& p : g->mem) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    }
+    g->bytes = 0;
+    DevGraph d;
+    d.n = g->dg.n;
+    d.arcs = g->dg.arcs;
+    d.directed = g->dg.directed;
+    d.weighted = g->dg.weighted;
+    g->dg = d;
+}
+
 extern "C" cc_status cc_graph_upload(cc_context* ctx, int64_t n, int64_t arcs, const int64_t* row_ptr,
                                      const int32_t* col_idx, const int32_t* w, uint32_t flags, cc_graph** out) {
     if (!ctx || !out || !row_ptr || (arcs > 0 && !col_idx)) return fail(CC_EINVAL, "cc_graph_upload: null argument");
@@ -875,7 +1012,12 @@ extern "C" cc_status cc_graph_upload(cc_context* ctx, int64_t n, int64_t arcs, c
         std::vector<int32_t> pstart;
         if (w) {
             std::vector<int32_t> order;
-            if (grow_patches(n, row_ptr, col_idx, order, pstart)) orig.swap(order);
+            bool cut = false;
+            try {
+                cut = grow_patches(n, row_ptr, col_idx, order, pstart);
+            } catch (const std::bad_alloc&) {
+            }
+            if (cut) orig.swap(order);
             else pstart.clear();
         }
         if (!w)
@@ -908,113 +1050,21 @@ extern "C" cc_status cc_graph_upload(cc_context* ctx, int64_t n, int64_t arcs, c
                 return first_hub[(size_t)a] < first_hub[(size_t)b];
             });
         }
-        g->inv.assign((size_t)n, 0);
-        for (int64_t i = 0; i < n; i++) g->inv[(size_t)orig[(size_t)i]] = (int32_t)i;
-        // ---- relabelled out-arcs
-        std::vector<uint32_t> rp((size_t)n + 1, 0);
-        std::vector<int32_t> col((size_t)arcs), ww(w ? (size_t)arcs : 0);
-        for (int64_t i = 0; i < n; i++) {
-            const int64_t v = orig[(size_t)i];
-            rp[(size_t)i + 1] = rp[(size_t)i] + (uint32_t)(row_ptr[v + 1] - row_ptr[v]);
-        }
-        parallel_ranges(0, n, [&](int64_t i0, int64_t i1) {
-            for (int64_t i = i0; i < i1; i++) {
-                const int64_t v = orig[(size_t)i];
-                uint32_t q = rp[(size_t)i];
-                for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; e++, q++) {
-                    col[q] = g->inv[(size_t)col_idx[e]];
-                    if (w) ww[q] = w[e];
-                }
-                // rows in id order: a chunk's lanes then read neighbouring masks
-                if (!w) std::sort(col.begin() + rp[(size_t)i], col.begin() + rp[(size_t)i + 1]);
-            }
-        });
-        std::vector<uint32_t> trp;
-        std::vector<int32_t> tcol, tw;
-        if (directed) transpose_host(n, rp, col, ww, trp, tcol, tw);
-        // ---- hub prefix (by in-degree of the pull direction; for digraphs by
-        //      the larger of the two, ids being sorted by total degree)
-        const std::vector<uint32_t>& prp = directed ? trp : rp;
-        int64_t hubs = 0;
-        for (int64_t i = 0; i < n; i++) {
-            const uint32_t din = prp[(size_t)i + 1] - prp[(size_t)i];
-            const uint32_t dout = rp[(size_t)i + 1] - rp[(size_t)i];
-            if (std::max(din, dout) > hub_degree(directed)) hubs = i + 1;
-        }
-        int64_t nh = (hubs + 63) / 64 * 64;
-        if (nh > n) nh = n;
-        if (w) nh = 0;
-        g->dg.nh = nh;
-        if (w) {
-            double sw = 0;
-            for (int64_t e = 0; e < arcs; e++) sw += w[e];
-            const double mean = arcs > 0 ? sw / (double)arcs : 1.0;
-            g->dg.delta = (uint32_t)std::max<double>(1.0, std::llround(1.5 * mean));
-        }
-        g->tune.delta = (int32_t)std::min<uint32_t>(std::max<uint32_t>(g->dg.delta, 1u), INT32_MAX);
-        std::vector<int32_t> ch_in = hub_chunk_list(prp, nh, hub_chunk(directed));
-        std::vector<int32_t> ch_out = directed ? hub_chunk_list(rp, nh, hub_chunk(directed)) : std::vector<int32_t>();
-        if (!directed) g->chunks_host = ch_in;
-
-        auto up = [&](int slot, const void* src, size_t bytes) -> void* {
-            void* d = nullptr;
-            hipError_t e = hipMalloc(&d, bytes ? bytes : 4);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                throw std::bad_alloc();
-            }
-            g->mem[slot] = d;
-            g->bytes += bytes;
-            if (bytes) CCG_HIP(hipMemcpy(d, src, bytes, hipMemcpyHostToDevice));
-            return d;
-        };
-        g->dg.rp = (const uint32_t*)up(0, rp.data(), sizeof(uint32_t) * (n + 1));
-        g->dg.col = (const int32_t*)up(1, col.data(), sizeof(int32_t) * arcs);
-        if (w) g->dg.w = (const int32_t*)up(2, ww.data(), sizeof(int32_t) * arcs);
-        if (directed) {
-            g->dg.rrp = (const uint32_t*)up(3, trp.data(), sizeof(uint32_t) * (n + 1));
-            g->dg.rcol = (const int32_t*)up(4, tcol.data(), sizeof(int32_t) * arcs);
-            if (w) g->dg.rw = (const int32_t*)up(5, tw.data(), sizeof(int32_t) * arcs);
-        } else {
-            g->dg.rrp = g->dg.rp;
-            g->dg.rcol = g->dg.col;
-            g->dg.rw = g->dg.w;
-        }
-        g->dg.orig = (const int32_t*)up(6, orig.data(), sizeof(int32_t) * n);
-        g->dg.inv = (const int32_t*)up(9, g->inv.data(), sizeof(int32_t) * n);
-        g->dg.hub_chunks_in = (const int32_t*)up(7, ch_in.data(), sizeof(int32_t) * ch_in.size());
-        g->dg.n_hub_chunks_in = (int32_t)(ch_in.size() / 3);
-        if (directed) {
-            g->dg.hub_chunks_out = (const int32_t*)up(8, ch_out.data(), sizeof(int32_t) * ch_out.size());
-            g->dg.n_hub_chunks_out = (int32_t)(ch_out.size() / 3);
-        } else {
-            g->dg.hub_chunks_out = g->dg.hub_chunks_in;
-            g->dg.n_hub_chunks_out = g->dg.n_hub_chunks_in;
-        }
-        if (w) zip_weighted(g, 10, 11, nullptr);
+        // a cut that cannot serve, or that memory does not hold, is no reason to
+        // refuse the graph: it is placed as one that cannot be cut
+        bool placed = false;
         if (!pstart.empty()) {
-            PatchGraph& pg = g->dg.patches;
-            int slot = 14;
-            auto take = [&](size_t bytes) -> void* {
-                void* d = nullptr;
-                if (hipMalloc(&d, bytes) != hipSuccess) {
-                    (void)hipGetLastError();
-                    throw std::bad_alloc();
-                }
-                g->mem[slot++] = d;
-                g->bytes += bytes;
-                return d;
-            };
-            pg.npatch = (int32_t)pstart.size() - 1;
-            pg.pstart = (const int32_t*)up(12, pstart.data(), sizeof(int32_t) * pstart.size());
-            int32_t* of = (int32_t*)take(sizeof(int32_t) * (size_t)n);
-            pg.patch_of = of;
-            build_patch_of(nullptr, pg.npatch, pg.pstart, of);
-            bool ok = build_patch_arcs(nullptr, pg, 0, g->dg.rp, g->dg.cw, take);
-            if (ok && directed) ok = build_patch_arcs(nullptr, pg, 1, g->dg.rrp, g->dg.rcw, take);
-            else if (ok) pg.dir[1] = pg.dir[0];
-            if (!ok) pg = PatchGraph{};  // a patch with too many neighbours: searched without patches
+            try {
+                placed = place_graph(g, row_ptr, col_idx, w, orig, pstart);
+            } catch (const std::bad_alloc&) {
+            }
+            if (!placed) {
+                drop_graph(g);
+                pstart.clear();
+                for (int64_t v = 0; v < n; v++) orig[(size_t)v] = (int32_t)v;
+            }
         }
+        if (!placed) place_graph(g, row_ptr, col_idx, w, orig, pstart);
     } catch (const std::bad_alloc&) {
         graph_unref(g);
         return fail(CC_ENOMEM, "cc_graph_upload: device allocation failed");

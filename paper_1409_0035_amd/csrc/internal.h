@@ -384,8 +384,12 @@ void sssp_weighted_batched_enqueue(hipStream_t st, const uint32_t* rp, const int
                                    void* scratch, size_t scratch_size, DevFlags* flags, uint32_t* maxd_out);
 // The same searches patch by patch (sssp_patch.hip)
 void build_patch_of(hipStream_t st, int32_t npatch, const int32_t* pstart, int32_t* patch_of);
+struct PatchMemory {  // device memory that the graph keeps, and what it gives back
+    std::function<void*(size_t)> take;
+    std::function<void(void*, size_t)> drop;
+};
 bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, const int2* cw,
-                      const std::function<void*(size_t)>& alloc);
+                      const PatchMemory& mem);
 size_t patch_scratch(int32_t kg, int32_t npatch);
 int sssp_patch(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const int32_t* samples_dev, int32_t kg,
                uint32_t* Dt, uint32_t step, void* scratch, size_t scratch_size, int32_t* hint, int64_t* maxd,

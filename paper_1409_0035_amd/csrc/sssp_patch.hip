@@ -541,15 +541,16 @@ size_t patch_scratch(int32_t kg, int32_t npatch) {
 
 // The patches' arcs of one direction, from its rows: slots, the arcs that do
 // not fit them (counted first), those by the patch they lead into, and the
-// neighbouring patches.  `alloc` gives device memory that the caller keeps.
-// False when some patch has too many neighbours.
+// neighbouring patches.  `mem` gives device memory that the caller keeps (and
+// frees, also what was taken when this fails).  False when some patch has too
+// many neighbours.
 bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, const int2* cw,
-                      const std::function<void*(size_t)>& alloc) {
+                      const PatchMemory& mem) {
     const size_t np = (size_t)g.npatch;
     const dim3 grid((unsigned)g.npatch);
     PatchDir A;
-    uint32_t* ell = (uint32_t*)alloc(sizeof(uint32_t) * np * kPatchSlots * kPatchNodes);
-    int32_t* ptrs = (int32_t*)alloc(sizeof(int32_t) * (3 * (np + 1) + 1));  // eptr, iptr, cursor, bad, differ
+    uint32_t* ell = (uint32_t*)mem.take(sizeof(uint32_t) * np * kPatchSlots * kPatchNodes);
+    int32_t* ptrs = (int32_t*)mem.take(sizeof(int32_t) * (3 * (np + 1) + 1));  // eptr, iptr, cursor, bad, differ
     int32_t *eptr = ptrs, *iptr = ptrs + np + 1, *cursor = iptr + np + 1;
     hipLaunchKernelGGL(k_patch_clear, dim3(256), dim3(256), 0, st, ptrs, (int64_t)(3 * (np + 1) + 1));
     hipLaunchKernelGGL(k_patch_arcs, grid, dim3(kPatchNodes), 0, st, rp, cw, g.pstart, g.patch_of, ell, eptr, iptr,
@@ -569,9 +570,9 @@ bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, 
     }
     CCG_HIP(hipMemcpyAsync(ptrs, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice, st));
     const size_t bytes = sizeof(uint4) * (size_t)std::max<int64_t>(at, 1);
-    uint4 *ext = (uint4*)alloc(bytes), *in = (uint4*)alloc(bytes);
-    int32_t* from = (int32_t*)alloc(sizeof(int32_t) * np * kPatchNb);
-    int64_t* to = (int64_t*)alloc(sizeof(int64_t) * np * kPatchNb);
+    uint4 *ext = (uint4*)mem.take(bytes), *in = (uint4*)mem.take(bytes);
+    int32_t* from = (int32_t*)mem.take(sizeof(int32_t) * np * kPatchNb);
+    int64_t* to = (int64_t*)mem.take(sizeof(int64_t) * np * kPatchNb);
     hipLaunchKernelGGL(k_patch_arcs, grid, dim3(kPatchNodes), 0, st, rp, cw, g.pstart, g.patch_of, (uint32_t*)nullptr,
                        (int32_t*)nullptr, (int32_t*)nullptr, (const int32_t*)eptr, ext);
     hipLaunchKernelGGL(k_patch_into, grid, dim3(256), 0, st, g.pstart, (const int32_t*)eptr, (const uint4*)ext,

@@ -13,17 +13,16 @@ enum { OK = 0, NO_MEMORY = 2, NOT_SUPPORTED = 801, MAXP = 1 << 16, MAXL = 1 << 1
 static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static void* ptr[MAXP];
 static size_t len[MAXP], live, peak;
-static int64_t allocs, fail_from = INT64_MAX, fail_to = INT64_MAX;
+static size_t limit = SIZE_MAX; /* allocations that would pass it are refused */
 static int sync_us;
 typedef struct { const void* func; int64_t set, used; } lds_t;
 static lds_t lds[MAXL];
 static int nlds;
 
-int64_t fake_allocs(void) { return allocs; }
 size_t fake_live(void) { return live; }
 size_t fake_peak(void) { return peak; }
 void fake_reset_peak(void) { peak = live; }
-void fake_fail(int64_t from, int64_t to) { fail_from = from; fail_to = to; } /* allocations [from, to) are refused */
+void fake_limit(size_t bytes) { limit = bytes; }
 void fake_sync_us(int us) { sync_us = us; }
 int fake_lds(int i, const void** func, int64_t* set, int64_t* used) {
     if (i >= nlds) return 0;
@@ -34,9 +33,8 @@ int fake_lds(int i, const void** func, int64_t* set, int64_t* used) {
 int hipMalloc(void** p, size_t n) {
     int i = 0, rc = NO_MEMORY;
     pthread_mutex_lock(&mu);
-    const int64_t at = allocs++;
     *p = NULL;
-    if (at < fail_from || at >= fail_to) {
+    if (live + n <= limit) {
         while (i < MAXP && ptr[i]) i++;
         void* q = i < MAXP ? aligned_alloc(256, (n + 256) / 256 * 256) : NULL;
         if (q) {

@@ -19,13 +19,12 @@ def fake_lib(tmp_path_factory):
     return so
 
 
-def _run(fake_lib, body):
+def _run(fake_lib, *body):
     head = """
         import ctypes, os, sys
         fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # before torch's runtime: its functions are found first
         fake.fake_live.restype = fake.fake_peak.restype = ctypes.c_size_t
-        fake.fake_allocs.restype = ctypes.c_int64
-        fake.fake_fail.argtypes = [ctypes.c_int64, ctypes.c_int64]
+        fake.fake_limit.argtypes = [ctypes.c_size_t]
         import numpy as np
         import graphgen
         import paper_1409_0035_amd as cc
@@ -38,7 +37,7 @@ def _run(fake_lib, body):
 
         ctx = cc.Context(0)
     """
-    code = textwrap.dedent(head) + textwrap.dedent(body)
+    code = textwrap.dedent(head) + "".join(textwrap.dedent(b) for b in body)
     p = subprocess.run([sys.executable, "-c", code, fake_lib], cwd=ROOT, timeout=110, capture_output=True, text=True)
     assert p.returncode == 0, p.stdout + p.stderr
 
@@ -63,4 +62,36 @@ def test_lds_limit_of_a_kernel_is_one_value(fake_lib):
                 assert used <= limit[f]
                 launches += 1
         assert launches >= 3
+    """)
+
+
+# bytes a weighted graph keeps on the device: row bounds, ends, lengths, the two id maps, one word where a list of hub
+# chunks is empty, (end, length) pairs; with the arcs reversed once more for a digraph
+WEIGHTED_BYTES = """
+        def weighted_bytes(g):
+            one = 4 * (g.n + 1) + 4 * g.arcs + 4 * g.arcs + 8 * g.arcs
+            return one * (2 if g.directed else 1) + 2 * 4 * g.n + (8 if g.directed else 4)
+"""
+
+
+def test_upload_without_memory_for_patches(fake_lib):
+    """The patch tables are an optimisation: where memory holds the graph but
+    not them, the graph is accepted without, and nothing of the attempt stays."""
+    _run(fake_lib, WEIGHTED_BYTES, """
+        und = graphgen.grid(60, 70, 8, 0.1, 1, 1000, seed=1)
+        for g in (und, graphgen.with_lengths(graphgen.symmetric_digraph(graphgen.grid(60, 70, 4)), 1, 50, 8)):
+            need, before = weighted_bytes(g), fake.fake_live()
+            for spare in (0, 1, 10_000, 50_000, 150_000):  # the tables take more
+                fake.fake_limit(before + need + spare)
+                gh = ctx.upload(g)
+                assert fake.fake_live() - before == need, (g.directed, spare)
+                ctx.release(gh)
+                assert fake.fake_live() == before
+            fake.fake_limit(before + need - 1)
+            try:
+                ctx.upload(g)
+                raise SystemExit("a graph without room was accepted")
+            except cc.CCError as e:
+                assert e.status == cc.CC_ENOMEM
+            assert fake.fake_live() == before
     """)

@@ -587,6 +587,8 @@ bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, 
     CCG_HIP(hipMemcpyAsync(hb, bad, sizeof(hb), hipMemcpyDeviceToHost, st));
     CCG_HIP(hipStreamSynchronize(st));
     if (hb[0]) return false;
+    mem.drop(from, sizeof(int32_t) * np * kPatchNb);  // read by k_patch_to only
+    if (!hb[1]) mem.drop(in, bytes);                  // ext serves both
     A.ell = ell;
     A.eptr = eptr;
     A.ext = ext;

@@ -326,12 +326,6 @@ __global__ void k_small_errest_done(const DevFlags* __restrict__ flags, DevFlags
         __hip_atomic_store(stamp, (uint32_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Share of a weighted graph's arcs inside patches from which it is searched by
-// them.  Grids of degree 4-8 lie at 0.91 (2048 x 2048, 64 samples: 48 ms
-// against 136); preferential attachment, R-MAT and uniform random graphs of
-// 4-13 arcs a node lie at 0.16-0.31, where most relaxations would be offers and
-// patches have too many neighbours.  No generator here falls between.
-constexpr double kPatchInside = 0.6;
 constexpr int32_t kStagedSamples = 256;  // samples of an estimate that can be replayed from a captured graph
 
 struct Lane {
@@ -766,8 +760,8 @@ void transpose_host(int64_t n, const std::vector<uint32_t>& rp, const std::vecto
 // Cuts a graph into patches of up to kPatchNodes nodes, grown breadth-first
 // from the lowest id left (so a row-major grid gets near-squares): order lists
 // the nodes patch by patch, pstart where each begins.  False when too few
-// arcs would stay inside (denser or unlocal graphs), which the first patches
-// show.
+// arcs would find a slot inside (denser or unlocal graphs), which the first
+// patches show; the patch tables' build looks at all of them.
 static bool grow_patches(int64_t n, const int64_t* rp, const int32_t* col, std::vector<int32_t>& order,
                          std::vector<int32_t>& pstart) {
     constexpr int64_t kLook = 64 * kPatchNodes;  // nodes after which the share is first looked at
@@ -776,14 +770,16 @@ static bool grow_patches(int64_t n, const int64_t* rp, const int32_t* col, std::
     order.reserve((size_t)n);
     pstart.assign(1, 0);
     std::vector<int32_t> patch((size_t)n, -1);
-    auto inside = [&]() {  // arcs of the patches so far that stay in their patch, against all of theirs
-        int64_t in = 0, all = 0;
-        for (int32_t v : order)
-            for (int64_t e = rp[v]; e < rp[v + 1]; e++) {
-                all++;
-                in += patch[(size_t)col[e]] == patch[(size_t)v];
-            }
-        return all == 0 ? 0.0 : (double)in / (double)all;
+    auto serves = [&]() {  // the arcs of the patches so far
+        int64_t slots = 0, spilled = 0, all = 0;
+        for (int32_t v : order) {
+            int64_t in = 0;
+            for (int64_t e = rp[v]; e < rp[v + 1]; e++) in += patch[(size_t)col[e]] == patch[(size_t)v];
+            all += rp[v + 1] - rp[v];
+            slots += std::min<int64_t>(in, kPatchSlots);
+            spilled += std::max<int64_t>(in - kPatchSlots, 0);
+        }
+        return patches_serve(all, slots, spilled);
     };
     int64_t seed = 0;
     bool looked = false;
@@ -811,10 +807,10 @@ static bool grow_patches(int64_t n, const int64_t* rp, const int32_t* col, std::
         pstart.push_back((int32_t)order.size());
         if (!looked && (int64_t)order.size() >= kLook) {
             looked = true;
-            if (inside() < kPatchInside) return false;
+            if (!serves()) return false;
         }
     }
-    return looked || inside() >= kPatchInside;
+    return looked || serves();
 }
 
 // The (end, length) pairs the batched weighted searches read, for both
@@ -838,8 +834,7 @@ static void zip_weighted(cc_graph* g, int a, int b, hipStream_t st) {
 
 // Puts a graph on the device with its nodes in the order `orig` (and, unless
 // pstart is empty, cut into those patches): relabelled arcs of both directions,
-// hub chunks, id maps, patch tables.  False when the patches cannot serve (one
-// has too many neighbours).
+// hub chunks, id maps, patch tables.  False when the patches cannot serve.
 static bool place_graph(cc_graph* g, const int64_t* row_ptr, const int32_t* col_idx, const int32_t* w,
                         const std::vector<int32_t>& orig, const std::vector<int32_t>& pstart) {
     const int64_t n = g->dg.n, arcs = g->dg.arcs;
@@ -953,9 +948,9 @@ static bool place_graph(cc_graph* g, const int64_t* row_ptr, const int32_t* col_
     int32_t* of = (int32_t*)mem.take(sizeof(int32_t) * (size_t)n);
     pg.patch_of = of;
     build_patch_of(nullptr, pg.npatch, pg.pstart, of);
-    if (!build_patch_arcs(nullptr, pg, 0, g->dg.rp, g->dg.cw, mem)) return false;
+    if (!build_patch_arcs(nullptr, pg, 0, arcs, g->dg.rp, g->dg.cw, mem)) return false;
     if (!directed) pg.dir[1] = pg.dir[0];
-    return !directed || build_patch_arcs(nullptr, pg, 1, g->dg.rrp, g->dg.rcw, mem);
+    return !directed || build_patch_arcs(nullptr, pg, 1, arcs, g->dg.rrp, g->dg.rcw, mem);
 }
 
 // What place_graph put on the device, given back.

@@ -143,6 +143,23 @@ constexpr int kPatchSlots = 8;
 constexpr int kPatchNb = 32;  // neighbouring patches, and a patch's own slot
 constexpr int32_t kPatchRounds = 16384;
 constexpr int32_t kPatchSamples = 512;  // per call: eight groups of at most a wave's lanes
+// Whether a graph is searched by its patches: by the share of its arcs that
+// have a slot inside a patch, and of those that lie inside one and find none (a
+// node has kPatchSlots; lengths from 2^24 - 1 on fit none).  These go through the
+// rounds like arcs between patches, and a front that needs them crosses a patch
+// in many rounds instead of one.  k_wsearch against patches in ms, 64 samples:
+// grids of degree 4-8 (0.91 in slots; 2048 x 2048) 136 against 48; 30 x 30 x 30
+// mesh (0.76) 1.7 / 1.3.  Random geometric graphs of 30,000 nodes: mean degree 5
+// (0.94, 0.02 without slot) 4.5 / 1.8, 7 (0.85, 0.08) 3.6 / 2.1; 9 (0.76, 0.15)
+// 3.3 / 3.0 and 4.3 / 6.2 with 256 samples; 10.5 (0.69, 0.21) 3.3 / 3.8 and
+// 4.3 / 8.2.  Rings of 60,000 nodes, each joined to the next 4 (0.99, 0) 48 / 7.8,
+// to the next 5 (0.80, 0.19) 57 / 219.  Preferential attachment, R-MAT and uniform
+// random graphs of 4-13 arcs a node lie at 0.16-0.31 in slots, where most
+// relaxations would be offers and patches have too many neighbours.
+constexpr double kPatchInside = 0.6, kPatchSpilled = 0.1;
+inline bool patches_serve(int64_t arcs, int64_t slots, int64_t spilled) {
+    return (double)slots >= kPatchInside * (double)arcs && (double)spilled <= kPatchSpilled * (double)arcs;
+}
 struct PatchDir {
     const uint32_t* ell = nullptr;  // [npatch][kPatchSlots][kPatchNodes] weight << 8 | end within the patch
     const int32_t* eptr = nullptr;  // [npatch + 1] a patch's outside arcs in ext
@@ -388,7 +405,7 @@ struct PatchMemory {  // device memory that the graph keeps, and what it gives b
     std::function<void*(size_t)> take;
     std::function<void(void*, size_t)> drop;
 };
-bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, const int2* cw,
+bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, int64_t arcs, const uint32_t* rp, const int2* cw,
                       const PatchMemory& mem);
 size_t patch_scratch(int32_t kg, int32_t npatch);
 int sssp_patch(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const int32_t* samples_dev, int32_t kg,

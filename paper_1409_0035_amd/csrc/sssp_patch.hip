@@ -63,17 +63,18 @@ __global__ void k_patch_of(const int32_t* __restrict__ pstart, int32_t* patch_of
 // One block per patch, a thread per node: the inner arcs into the node's
 // slots (weight << 8 | local end), and the number of the others.  With ext set,
 // those others in full instead, from eptr[p] on (end, weight, start within the
-// patch, end's patch).  ecount[q]: arcs of that kind into patch q (a node's
-// inner arcs beyond its slots among them, as arcs from the patch to itself).
+// patch, end's patch).  icount[q]: arcs of that kind into patch q (a node's
+// inner arcs beyond its slots among them, as arcs from the patch to itself;
+// *spilled counts those).
 __global__ __launch_bounds__(kPatchNodes) void k_patch_arcs(const uint32_t* __restrict__ rp,
                                                             const int2* __restrict__ cw,
                                                             const int32_t* __restrict__ pstart,
                                                             const int32_t* __restrict__ patch_of, uint32_t* ell,
-                                                            int32_t* count, int32_t* icount,
+                                                            int32_t* count, int32_t* icount, int32_t* spilled,
                                                             const int32_t* __restrict__ eptr, uint4* ext) {
-    __shared__ int32_t s_n;
+    __shared__ int32_t s_n, s_spilled;
     const int32_t p = blockIdx.x, j = threadIdx.x, ps = pstart[p], pe = pstart[p + 1], v = ps + j;
-    if (j == 0) s_n = 0;
+    if (j == 0) s_n = s_spilled = 0;
     __syncthreads();
     int slot = 0;
     if (v < pe) {
@@ -86,7 +87,10 @@ __global__ __launch_bounds__(kPatchNodes) void k_patch_arcs(const uint32_t* __re
             } else {
                 const int32_t at = atomicAdd(&s_n, 1), q = patch_of[x.x];
                 if (ext) ext[eptr[p] + at] = make_uint4((uint32_t)x.x, (uint32_t)x.y, (uint32_t)j, (uint32_t)q);
-                else atomicAdd(&icount[q], 1);
+                else {
+                    atomicAdd(&icount[q], 1);
+                    if (q == p) atomicAdd(&s_spilled, 1);
+                }
             }
         }
     }
@@ -94,7 +98,10 @@ __global__ __launch_bounds__(kPatchNodes) void k_patch_arcs(const uint32_t* __re
         for (; slot < kPatchSlots; slot++)
             ell[((int64_t)p * kPatchSlots + slot) * kPatchNodes + j] = kNoWeight << 8 | (uint32_t)j;
         __syncthreads();
-        if (j == 0) count[p] = s_n;
+        if (j == 0) {
+            count[p] = s_n;
+            if (s_spilled) atomicAdd(spilled, s_spilled);
+        }
     }
 }
 
@@ -542,20 +549,20 @@ size_t patch_scratch(int32_t kg, int32_t npatch) {
 // The patches' arcs of one direction, from its rows: slots, the arcs that do
 // not fit them (counted first), those by the patch they lead into, and the
 // neighbouring patches.  `mem` gives device memory that the caller keeps (and
-// frees, also what was taken when this fails).  False when some patch has too
-// many neighbours.
-bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, const int2* cw,
+// frees, also what was taken when this fails).  False when the patches do not
+// serve: too few arcs in slots, or a patch with too many neighbours.
+bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, int64_t arcs, const uint32_t* rp, const int2* cw,
                       const PatchMemory& mem) {
     const size_t np = (size_t)g.npatch;
     const dim3 grid((unsigned)g.npatch);
     PatchDir A;
     uint32_t* ell = (uint32_t*)mem.take(sizeof(uint32_t) * np * kPatchSlots * kPatchNodes);
-    int32_t* ptrs = (int32_t*)mem.take(sizeof(int32_t) * (3 * (np + 1) + 1));  // eptr, iptr, cursor, bad, differ
-    int32_t *eptr = ptrs, *iptr = ptrs + np + 1, *cursor = iptr + np + 1;
-    hipLaunchKernelGGL(k_patch_clear, dim3(256), dim3(256), 0, st, ptrs, (int64_t)(3 * (np + 1) + 1));
+    int32_t* ptrs = (int32_t*)mem.take(sizeof(int32_t) * (3 * (np + 1) + 2));  // eptr, iptr, spilled, cursor, bad, differ
+    int32_t *eptr = ptrs, *iptr = ptrs + np + 1, *spilled = iptr + np + 1, *cursor = spilled + 1;
+    hipLaunchKernelGGL(k_patch_clear, dim3(256), dim3(256), 0, st, ptrs, (int64_t)(3 * (np + 1) + 2));
     hipLaunchKernelGGL(k_patch_arcs, grid, dim3(kPatchNodes), 0, st, rp, cw, g.pstart, g.patch_of, ell, eptr, iptr,
-                       (const int32_t*)nullptr, (uint4*)nullptr);
-    std::vector<int32_t> h(2 * (np + 1));
+                       spilled, (const int32_t*)nullptr, (uint4*)nullptr);
+    std::vector<int32_t> h(2 * (np + 1) + 1);
     CCG_HIP(hipMemcpyAsync(h.data(), ptrs, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost, st));
     CCG_HIP(hipStreamSynchronize(st));
     int64_t at = 0;
@@ -568,13 +575,14 @@ bool build_patch_arcs(hipStream_t st, PatchGraph& g, int d, const uint32_t* rp, 
             at += count;
         }
     }
+    if (!patches_serve(arcs, arcs - at, h.back())) return false;
     CCG_HIP(hipMemcpyAsync(ptrs, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice, st));
     const size_t bytes = sizeof(uint4) * (size_t)std::max<int64_t>(at, 1);
     uint4 *ext = (uint4*)mem.take(bytes), *in = (uint4*)mem.take(bytes);
     int32_t* from = (int32_t*)mem.take(sizeof(int32_t) * np * kPatchNb);
     int64_t* to = (int64_t*)mem.take(sizeof(int64_t) * np * kPatchNb);
     hipLaunchKernelGGL(k_patch_arcs, grid, dim3(kPatchNodes), 0, st, rp, cw, g.pstart, g.patch_of, (uint32_t*)nullptr,
-                       (int32_t*)nullptr, (int32_t*)nullptr, (const int32_t*)eptr, ext);
+                       (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr, (const int32_t*)eptr, ext);
     hipLaunchKernelGGL(k_patch_into, grid, dim3(256), 0, st, g.pstart, (const int32_t*)eptr, (const uint4*)ext,
                        (const int32_t*)iptr, cursor, in);
     int32_t* bad = cursor + np;  // two counters, cleared, past the cursors

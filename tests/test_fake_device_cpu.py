@@ -106,7 +106,7 @@ def test_upload_keeps_the_patch_tables_it_uses(fake_lib):
         g, before = graphgen.grid(16, 32, 8, 0.1, 1, 1000, seed=1), fake.fake_live()
         gh = ctx.upload(g)
         patches = [np_ for np_ in range(2, 12) if fake.fake_live() - before - weighted_bytes(g) ==
-                   4 * (np_ + 1) + 4 * g.n + 32 * 256 * np_ + 4 * (3 * (np_ + 1) + 1) + 16 + 8 * 32 * np_]
+                   4 * (np_ + 1) + 4 * g.n + 32 * 256 * np_ + 4 * (3 * (np_ + 1) + 2) + 16 + 8 * 32 * np_]
         assert len(patches) == 1, fake.fake_live() - before - weighted_bytes(g)
         ctx.release(gh)
         assert fake.fake_live() == before

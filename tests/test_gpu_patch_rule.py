@@ -47,3 +47,64 @@ def test_patch_with_many_neighbours(joined, search, directed):
     """A patch next to 31 others at most has a slot in each; past that the
     graph is searched without patches, in the caller's order."""
     _check(_strip_with_hub(joined, directed), 12, search)
+
+
+def _ring(n, reach):
+    i = np.repeat(np.arange(n), reach)
+    j = (i + np.tile(np.arange(1, reach + 1), n)) % n
+    return graphgen.csr_from_arcs(n, i, j, np.random.default_rng(reach).integers(1, 1000, i.size).astype(np.int32))
+
+
+def _grid_with_extras(every):
+    """A grid of eight neighbours, every so-many-th node also joined to the next but one: two arcs without a slot."""
+    g = graphgen.grid(30, 40, 8)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    keep = src < g.col_idx
+    v = np.arange(0, g.n - 2, every)
+    v = v[v % 40 < 38]
+    s, d = np.concatenate([src[keep], v]), np.concatenate([g.col_idx[keep], v + 2])
+    return graphgen.csr_from_arcs(g.n, s, d, np.random.default_rng(every).integers(1, 1000, s.size).astype(np.int32))
+
+
+def _grid_with_wide_lengths(share):
+    """Lengths of 2^24 and more find no slot."""
+    g = graphgen.grid(16, 32, 8)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    keep = src < g.col_idx
+    r = np.random.default_rng(7)
+    w = np.where(r.random(int(keep.sum())) < share, 1 << 24, r.integers(1 << 20, 1 << 21, int(keep.sum())))
+    return graphgen.csr_from_arcs(g.n, src[keep], g.col_idx[keep], w.astype(np.int32))
+
+
+def _grid_then_random():
+    """64 patches of a grid first, which look well, then as many arcs between random nodes."""
+    g = graphgen.grid(128, 128, 4)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    keep = src < g.col_idx
+    r = np.random.default_rng(9)
+    m = 20_000
+    tail = g.n + np.arange(m)
+    s = np.concatenate([src[keep], tail, g.n + r.integers(0, m, 2 * m)])
+    d = np.concatenate([g.col_idx[keep], np.concatenate([[g.n - 1], tail[:-1]]), g.n + r.integers(0, m, 2 * m)])
+    return graphgen.csr_from_arcs(g.n + m, s, d, r.integers(1, 1000, s.size).astype(np.int32))
+
+
+RULE = {
+    "ring-4-all-in-slots": (lambda: _ring(1500, 4), cc.CC_SEARCH_PATCHES),
+    "ring-5-a-fifth-without": (lambda: _ring(1500, 5), cc.CC_SEARCH_WEIGHTED),
+    "ring-6-a-third-without": (lambda: _ring(1500, 6), cc.CC_SEARCH_WEIGHTED),
+    "grid-a-few-without": (lambda: _grid_with_extras(5), cc.CC_SEARCH_PATCHES),
+    "grid-an-eighth-without": (lambda: _grid_with_extras(1), cc.CC_SEARCH_WEIGHTED),
+    "wide-lengths-a-few": (lambda: _grid_with_wide_lengths(0.05), cc.CC_SEARCH_PATCHES),
+    "wide-lengths-a-fifth": (lambda: _grid_with_wide_lengths(0.2), cc.CC_SEARCH_WEIGHTED),
+    "grid-then-random": (_grid_then_random, cc.CC_SEARCH_WEIGHTED),
+}
+
+
+@pytest.mark.parametrize("name", list(RULE))
+def test_arcs_without_a_slot(name):
+    """Arcs that lie inside a patch and find no slot there, up to a tenth of all
+    arcs; past that, and where later patches are not local, k_wsearch."""
+    make, search = RULE[name]
+    g = make()
+    _check(g, 9 if g.n > 5000 else 33, search)

@@ -473,7 +473,8 @@ struct cc_graph {
     bool borrowed = false;  // the arcs (and lengths) are the caller's device arrays, never freed here
     mutable std::atomic<int32_t> bfs_hint{0};  // levels the last batched traversal of this graph ran
     mutable std::atomic<int32_t> patch_hint[2] = {{0}, {0}};  // rounds the last searches by patches ran, by direction
-    mutable std::atomic<bool> patch_off{false};  // distances too large, or too many rounds, for the searches by patches
+    mutable std::atomic<bool> patch_off{false};  // distances too large for the searches by patches
+    mutable std::atomic<uint32_t> patch_short{0};  // the widest step (it follows the tuning) at which their rounds ran out
     mutable std::atomic<bool> small_deep{false};  // a distance passed 254: the small-graph searches cannot hold it
     cc_tuning tune{4, 1024, 8192, 1, 1024, 64};  // launch shapes (cc_graph_set_tuning / cc_autotune)
 };
@@ -1664,11 +1665,12 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
         }
         // weighted batched searches of up to 256 samples in one launch per direction can be captured
         const bool w_single = g.weighted && mode != CC_PLAIN && kw >= k && k <= kStagedSamples;
-        bool patched = g.weighted && mode != CC_PLAIN && g.patches.npatch > 0 &&
-                       !gr->patch_off.load(std::memory_order_relaxed);
-        if (patched) kw = std::min(kw, kPatchSamples);
         // the patches' rounds reach 16 bucket widths past a sample's least wait
         const uint32_t patch_step = (uint32_t)std::min<int64_t>(16 * (int64_t)std::max(1, gr->tune.delta), INT32_MAX);
+        bool patched = g.weighted && mode != CC_PLAIN && g.patches.npatch > 0 &&
+                       !gr->patch_off.load(std::memory_order_relaxed) &&
+                       patch_step > gr->patch_short.load(std::memory_order_relaxed);
+        if (patched) kw = std::min(kw, kPatchSamples);
         size_t trav_scratch;
         if (g.weighted)
             trav_scratch = mode == CC_PLAIN ? sssp_weighted_scratch(n, 1)
@@ -1870,10 +1872,13 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                         wr = sssp_patch(st, g.patches, dir, n, samples_dev + s0, kg, (uint32_t*)Dt + (size_t)s0 * n,
                                         patch_step, ts, trav_scratch, &hint, &md, &ds);
                         gr->patch_hint[dir].store(hint, std::memory_order_relaxed);
-                        if (wr == 4) {  // near the limit of distances, or too deep: as without patches
-                            patched = false;
-                            gr->patch_off.store(true, std::memory_order_relaxed);
+                        if (wr == 4) gr->patch_off.store(true, std::memory_order_relaxed);
+                        if (wr == 6) {
+                            uint32_t seen = gr->patch_short.load(std::memory_order_relaxed);
+                            while (seen < patch_step && !gr->patch_short.compare_exchange_weak(seen, patch_step)) {
+                            }
                         }
+                        if (wr == 4 || wr == 6) patched = false;  // as without patches
                     }
                     if (!patched)
                         wr = mode == CC_PLAIN

@@ -612,7 +612,7 @@ void build_patch_of(hipStream_t st, int32_t npatch, const int32_t* pstart, int32
 }
 
 // The searches of kg samples into Dt[j][v].  Returns 0 = done, 2 = unreached
-// node, 4 = a distance too near the limit or more rounds than kPatchRounds
+// node, 4 = a distance too near the limit, 6 = more rounds than kPatchRounds
 // (the caller then runs the general searches).  *hint: rounds to enqueue
 // before the first look, set to the rounds that ran.
 int sssp_patch(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const int32_t* samples_dev, int32_t kg,
@@ -640,7 +640,7 @@ int sssp_patch(hipStream_t st, const PatchGraph& g, int dir, int64_t n, const in
     stats->kernel_ms += kt.ms();
     stats->kernel_launches += done;
     stats->launches += done + 4;
-    if (left()) return 4;
+    if (left()) return 6;
     find_max(st, B, n * kg, mx);
     std::vector<uint32_t> lows((size_t)kg * (done + 1));
     uint32_t hm[3];  // overflow, largest distance, unreached

@@ -108,3 +108,22 @@ def test_arcs_without_a_slot(name):
     make, search = RULE[name]
     g = make()
     _check(g, 9 if g.n > 5000 else 33, search)
+
+
+def test_rounds_that_run_out_belong_to_the_setting():
+    """A bucket width of 1 lets a front over 1,000 x 1,000 nodes advance so little
+    that the rounds run out; the next estimate at the default width goes by
+    patches again, and both agree."""
+    g = graphgen.grid(1000, 1000, 8, 0.1, 1, 100_000, seed=1)
+    with cc.Context(0) as ctx:
+        gh = ctx.upload(g)
+        width = cc.cc_graph_get_tuning(gh)["delta"]
+        got = []
+        for delta, search in ((1, cc.CC_SEARCH_WEIGHTED), (width, cc.CC_SEARCH_PATCHES)):
+            cc.cc_graph_set_tuning(gh, delta=delta)
+            got.append(cc.cc_estimate(ctx.handle, gh, 1, seed=1, outputs=("delta", "src_sum")))
+            t = cc.cc_last_timing(ctx.handle)
+            print(f"  width {delta}: search {t['search']}, {t['levels']} rounds, {t['total_ms']:.1f} ms", flush=True)
+            assert t["search"] == search
+        assert np.array_equal(got[0]["delta"], got[1]["delta"]) and got[0]["src_sum"][0] == got[1]["src_sum"][0]
+        ctx.release(gh)

@@ -44,11 +44,14 @@ constexpr int kPBlock = 256;
 constexpr int kPWaves = kPBlock / 64;
 constexpr uint32_t kInf = 0xFFFFFFFFu;
 constexpr uint32_t kMaxDist = 0x7FFFFFFEu;
-// Samples are dealt to eight groups, and a group's blocks have block indices
-// congruent mod 8: workgroups go to the eight XCDs in turn, so a sample's
-// distances, offers and round state stay in one XCD's L2.
-constexpr int kGroups = 8;
+// Samples are dealt to groups, eight or a power of two more, and a group's
+// blocks have block indices congruent mod their number: workgroups go to the
+// eight XCDs in turn, so a sample's distances, offers and round state stay in
+// one XCD's L2.
+constexpr int kLgGroups = 3;
 constexpr int kLook = 64;           // patches a block looks after
+constexpr int64_t kPatchBlocks = 512; // fewer blocks than this leave CUs idle
+constexpr int32_t kPatchTurn = 4;     // samples of a group that a block's waves take at once
 constexpr int kExt = 4;             // outside arcs a lane has in flight
 constexpr int kSelf = kPatchNb - 1; // the slot in which a patch passes on its own wait
 constexpr uint32_t kNoWeight = 0xFFFFFFu;  // an empty slot: never improves its own node
@@ -197,8 +200,9 @@ __global__ void k_patch_clear(int32_t* p, int64_t count) {
 
 struct Bufs {
     uint32_t* W;        // [kg][n] distances, written by the patch's own wave
-    uint32_t* wait[2];  // [kGroups][npatch][gs][kPatchNb] offers, by round parity (kInf: none)
-    uint8_t* flag[2];   // [kGroups][npatch] whether some sample of the pair's group waits
+    int32_t lg;         // log2 of the number of groups
+    uint32_t* wait[2];  // [groups][npatch][gs][kPatchNb] offers, by round parity (kInf: none)
+    uint8_t* flag[2];   // [groups][npatch] whether some sample of the pair's group waits
     uint32_t* low;      // [kPatchRounds + 1][kg] a sample's least wait, by round (kInf: its search is over)
     uint32_t* ovf;
 };
@@ -217,8 +221,8 @@ __global__ void k_patch_seed(Bufs B, const int32_t* __restrict__ samples, int32_
                              const int32_t* __restrict__ patch_of) {
     const int32_t s = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (s >= kg) return;
-    const int64_t at = (int64_t)(s % kGroups) * npatch + patch_of[samples[s]];
-    B.wait[0][(at * gs + s / kGroups) * kPatchNb + kSelf] = 0;
+    const int64_t at = (int64_t)(s & ((1 << B.lg) - 1)) * npatch + patch_of[samples[s]];
+    B.wait[0][(at * gs + (s >> B.lg)) * kPatchNb + kSelf] = 0;
     B.flag[0][at] = 1;
 }
 
@@ -233,8 +237,8 @@ template <bool SAME>
 __global__ __launch_bounds__(kPBlock) void k_patch_round(Bufs B, const int32_t* __restrict__ pstart, PatchDir A,
                                                          const int32_t* __restrict__ samples, int64_t n, int32_t kg,
                                                          int32_t npatch, int32_t gs, uint32_t step, int32_t r) {
-    const int32_t b = (int32_t)blockIdx.x / kGroups, g = (int32_t)blockIdx.x % kGroups;
-    const int32_t nb = (int32_t)gridDim.x / kGroups;
+    const int32_t lg = B.lg, b = (int32_t)blockIdx.x >> lg, g = (int32_t)blockIdx.x & ((1 << lg) - 1);
+    const int32_t nb = (int32_t)gridDim.x >> lg;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* flags = B.flag[r & 1] + (int64_t)g * npatch;
     const int32_t look = b + lane * nb;  // this lane's patch
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(kPBlock) void k_patch_round(Bufs B, const int32_t* 
     uint32_t* nxt = B.wait[(r + 1) & 1];
     uint8_t* nflag = B.flag[(r + 1) & 1];
     // a sample's bound: `step` past its least wait
-    const int32_t mine = lane * kGroups + g;  // this lane's sample
+    const int32_t mine = (lane << lg) + g;  // this lane's sample
     uint32_t* nlow = B.low + (int64_t)(r + 1) * kg;
     uint32_t bound = 0, low_seen = 0;
     if (lane < gs && mine < kg) {
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(kPBlock) void k_patch_round(Bufs B, const int32_t* 
                     const int64_t pair0 = (int64_t)g * npatch + b + (int64_t)i * nb;
                     nxt[(pair0 * gs + l) * kPatchNb + kSelf] = x[u];
                     nflag[pair0] = 1;
-                    if (x[u] < seen) atomicMin(&nlow[l * kGroups + g], x[u]);
+                    if (x[u] < seen) atomicMin(&nlow[(l << lg) + g], x[u]);
                 }
             }
         }
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(kPBlock) void k_patch_round(Bufs B, const int32_t* 
         turn = readlane32(turn, 0);
         if (turn >= count) break;
         const int32_t pair = __builtin_amdgcn_readfirstlane(s_pair[turn]);
-        const int32_t p = b + (pair >> 8) * nb, l = pair & 0xFF, s = l * kGroups + g;
+        const int32_t p = b + (pair >> 8) * nb, l = pair & 0xFF, s = (l << lg) + g;
         if (p != at_patch) {
             at_patch = p;
             ps = pstart[p];
@@ -484,22 +488,38 @@ __global__ void k_patch_fold(const uint32_t* low, int32_t kg, const uint32_t* ov
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// samples of a group: sample s is the (s / kGroups)-th of group s % kGroups
-int32_t group_size(int32_t kg) { return (kg + kGroups - 1) / kGroups; }
+// log2 of the number of groups: more than eight where that few blocks, one a
+// patch and group, would leave the device idle while a block's waves take many
+// samples in turn (us, k_wsearch / eight groups / this: 12 x 12 x 12 mesh, 8
+// patches, 256 samples 725 / 978 / 601; 23 x 23 grid, 3 patches, 256 samples
+// 625 / 632 / 468, 64 samples 510 / 424 / 382; 100 x 100 grid, 40 patches, 256
+// samples 1851 / 1893 / 1516).  From 64 patches on more groups lose: 30 x 30 x
+// 30 mesh, 107 patches, 64 samples 1362 with eight, 1773 with 16 -- a patch's
+// tables are then read by two blocks.
+int32_t lg_groups(int32_t npatch, int32_t kg) {
+    int32_t lg = kLgGroups;
+    while (lg < 6 && ((int64_t)npatch << lg) < kPatchBlocks && (kg >> lg) > kPatchTurn) lg++;
+    return lg;
+}
+
+// samples of a group: sample s is the (s / groups)-th of group s % groups
+int32_t group_size(int32_t kg, int32_t lg) { return (kg + (1 << lg) - 1) >> lg; }
 
 size_t wait_count(int32_t npatch, int32_t kg) {
-    return (size_t)npatch * kGroups * group_size(kg) * kPatchNb;
+    const int32_t lg = lg_groups(npatch, kg);
+    return ((size_t)npatch << lg) * group_size(kg, lg) * kPatchNb;
 }
 
 Bufs carve(void* scratch, int32_t kg, int32_t npatch, uint32_t* Dt, uint32_t** mx) {
     char* p = (char*)scratch;
     Bufs B;
     B.W = Dt;
+    B.lg = lg_groups(npatch, kg);
     for (int i = 0; i < 2; i++) {
         B.wait[i] = (uint32_t*)p;
         p += align256(sizeof(uint32_t) * wait_count(npatch, kg));
         B.flag[i] = (uint8_t*)p;
-        p += align256((size_t)npatch * kGroups);
+        p += align256((size_t)npatch << B.lg);
     }
     B.low = (uint32_t*)p;
     p += align256(sizeof(uint32_t) * (size_t)kg * (kPatchRounds + 1));
@@ -512,8 +532,8 @@ void start(hipStream_t st, const Bufs& B, const PatchGraph& g, int64_t n, const 
            int32_t nrounds) {
     const int64_t pairs = n * kg;
     hipLaunchKernelGGL(k_patch_init, dim3((unsigned)std::min<int64_t>((pairs + 255) / 256, 8192)), dim3(256), 0, st, B,
-                       pairs, (int64_t)wait_count(g.npatch, kg), (int64_t)g.npatch * kGroups, kg, nrounds);
-    hipLaunchKernelGGL(k_patch_seed, dim3((kg + 63) / 64), dim3(64), 0, st, B, samples_dev, kg, group_size(kg),
+                       pairs, (int64_t)wait_count(g.npatch, kg), (int64_t)g.npatch << B.lg, kg, nrounds);
+    hipLaunchKernelGGL(k_patch_seed, dim3((kg + 63) / 64), dim3(64), 0, st, B, samples_dev, kg, group_size(kg, B.lg),
                        g.npatch, g.patch_of);
 }
 
@@ -522,14 +542,14 @@ void rounds(hipStream_t st, const Bufs& B, const PatchGraph& g, int dir, int64_t
     // blocks of a group: 256 (2,048 in all) measured best, a block's waves then
     // passing improvements on within a round; never more than kLook patches a block
     const int32_t nb = std::max(std::min(g.npatch, 256), (g.npatch + kLook - 1) / kLook);
-    const dim3 grid((unsigned)(nb * kGroups)), block(kPBlock);
+    const dim3 grid((unsigned)(nb << B.lg)), block(kPBlock);
     for (int32_t r = from; r < to; r++) {
         if (g.dir[dir].in)
             hipLaunchKernelGGL((k_patch_round<false>), grid, block, 0, st, B, g.pstart, g.dir[dir], samples_dev, n, kg,
-                               g.npatch, group_size(kg), step, r);
+                               g.npatch, group_size(kg, B.lg), step, r);
         else
             hipLaunchKernelGGL((k_patch_round<true>), grid, block, 0, st, B, g.pstart, g.dir[dir], samples_dev, n, kg,
-                               g.npatch, group_size(kg), step, r);
+                               g.npatch, group_size(kg, B.lg), step, r);
     }
 }
 
@@ -542,7 +562,7 @@ void find_max(hipStream_t st, const Bufs& B, int64_t pairs, uint32_t* mx) {
 }  // namespace
 
 size_t patch_scratch(int32_t kg, int32_t npatch) {
-    return 2 * (align256(sizeof(uint32_t) * wait_count(npatch, kg)) + align256((size_t)npatch * kGroups)) +
+    return 2 * (align256(sizeof(uint32_t) * wait_count(npatch, kg)) + align256((size_t)npatch << lg_groups(npatch, kg))) +
            align256(sizeof(uint32_t) * (size_t)kg * (kPatchRounds + 1)) + 512 + 1024;
 }
 

@@ -127,3 +127,10 @@ def test_rounds_that_run_out_belong_to_the_setting():
             assert t["search"] == search
         assert np.array_equal(got[0]["delta"], got[1]["delta"]) and got[0]["src_sum"][0] == got[1]["src_sum"][0]
         ctx.release(gh)
+
+
+@pytest.mark.parametrize("k", [7, 39, 40, 79, 81, 159, 161, 321, 512, 513])
+def test_groups_of_samples(k):
+    """Few patches: samples in 8, 16, 32 or 64 groups (more from 40, 80, 160 samples
+    on, four a group at least), the last samples of a group missing."""
+    _check(graphgen.grid(20, 33, 8, 0.1, 1, 1000, seed=5), k, cc.CC_SEARCH_PATCHES)

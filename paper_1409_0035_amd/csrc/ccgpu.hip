@@ -1365,25 +1365,6 @@ float elapsed(hipEvent_t a, hipEvent_t b) {
     return ms;
 }
 
-// Device bytes one job needs (excluding the caller's outputs), for admission.
-size_t job_bytes(const DevGraph& g, int32_t k, int32_t mode, int db) {
-    const int64_t n = g.n;
-    const size_t dbytes = Carver::sz((size_t)n * k * db);
-    size_t b = Carver::sz(sizeof(int32_t) * k) * 2 + Carver::sz(sizeof(DevFlags)) + Carver::sz(sizeof(LevelCounters) * kCounterSlots) +
-               Carver::sz(sizeof(int32_t) * n);
-    if (g.weighted) {
-        b += dbytes * (g.directed ? 3 : 2) + (mode == CC_PLAIN ? sssp_weighted_scratch(n, 1) : sssp_wsearch_scratch(n, k));
-    } else if (mode == CC_PLAIN) {
-        b += dbytes * (g.directed ? 3 : 2) + bfs_plain_scratch(n, g.arcs, k);
-    } else {
-        const int32_t kg = std::min(k, 256);
-        b += bfs_batched_scratch(n, kg, g.nh) + (size_t)32 * n * ((kg + 63) / 64) * 8;
-        if (g.directed || k > 256) b += dbytes * (g.directed ? 2 : 1);
-    }
-    b += Carver::sz(sizeof(int64_t) * k) + Carver::sz(sizeof(int32_t) * (size_t)k * k);
-    return b;
-}
-
 void record_timing(cc_timing* timing, Lane& L, const TravStats& stats, int db, int32_t search) {
     if (!timing) return;
     timing->traverse_ms = elapsed(L.ev[0], L.ev[1]);
@@ -1459,6 +1440,48 @@ bool small_search_fits(const cc_graph* gr, const Resolved& r) {
            g.arcs <= kSmallArcs && !gr->small_deep.load(std::memory_order_relaxed);
 }
 
+bool wants_errors(const cc_result& out) {
+    return out.S_err || out.S_ad || out.S_ad_err || out.S_sweep || out.S_sweep_err;
+}
+
+// Device bytes of a small graph's estimate.
+size_t small_bytes(int32_t n, int32_t k, bool want_err) {
+    const int32_t npad = (n + 63) / 64 * 64, W = (k + 63) / 64;
+    return Carver::sz((size_t)k * npad) + Carver::sz((size_t)k * k) +
+           Carver::sz(sizeof(uint64_t) * (size_t)k * kSmallT * W) + Carver::sz(sizeof(int32_t) * k) * 2 +
+           Carver::sz(sizeof(int32_t) * (size_t)k * kSmallT) + Carver::sz(sizeof(int64_t) * (size_t)k * kSmallT) +
+           Carver::sz(sizeof(int64_t) * k) + Carver::sz(want_err ? (size_t)n * k : 0) +
+           Carver::sz(want_err ? sizeof(int32_t) * n : 0) + Carver::sz(sizeof(DevFlags)) +
+           (want_err ? Carver::sz(sweep_scratch_bytes(n, k)) : 0);
+}
+
+// Device bytes one job needs (excluding the caller's outputs), for admission.
+// The largest of the searches that it may run: a small graph's estimate and a
+// search by patches may both give way to the general one.
+size_t job_bytes(const cc_graph* gr, const Resolved& r, const cc_result& out) {
+    const DevGraph& g = gr->dg;
+    const int64_t n = g.n;
+    const int32_t k = r.k, mode = r.mode, db = g.weighted ? 4 : 1;
+    const size_t dbytes = Carver::sz((size_t)n * k * db);
+    size_t b = Carver::sz(sizeof(int32_t) * k) * 2 + Carver::sz(sizeof(DevFlags)) + Carver::sz(sizeof(LevelCounters) * kCounterSlots) +
+               Carver::sz(sizeof(int32_t) * n);
+    if (g.weighted) {
+        size_t search = mode == CC_PLAIN ? sssp_weighted_scratch(n, 1) : sssp_wsearch_scratch(n, k);
+        if (mode != CC_PLAIN && g.patches.npatch > 0)
+            search = std::max(search, patch_scratch(std::min(k, kPatchSamples), g.patches.npatch));
+        b += dbytes * (g.directed ? 3 : 2) + search;
+    } else if (mode == CC_PLAIN) {
+        b += dbytes * (g.directed ? 3 : 2) + bfs_plain_scratch(n, g.arcs, k);
+    } else {
+        const int32_t kg = std::min(k, 256);
+        b += bfs_batched_scratch(n, kg, g.nh) + (size_t)32 * n * ((kg + 63) / 64) * 8;
+        if (g.directed || k > 256) b += dbytes * (g.directed ? 2 : 1);
+    }
+    b += Carver::sz(sizeof(int64_t) * k) + Carver::sz(sizeof(int32_t) * (size_t)k * k);
+    if (small_search_fits(gr, r)) b = std::max(b, small_bytes((int32_t)n, k, wants_errors(out)));
+    return b;
+}
+
 double wall_clock_khz(int device) {
     static std::atomic<int> rate{0};
     int khz = rate.load(std::memory_order_relaxed);
@@ -1476,14 +1499,8 @@ bool run_small(cc_context* ctx, const cc_graph* gr, const Resolved& r, const std
                const cc_result* out, Lane& L, cc_timing* timing, cc_status* result) {
     const DevGraph& g = gr->dg;
     const int32_t n = (int32_t)g.n, k = r.k, npad = (n + 63) / 64 * 64, W = (k + 63) / 64;
-    const bool want_err = out->S_err || out->S_ad || out->S_ad_err || out->S_sweep || out->S_sweep_err;
-    const size_t rows = want_err ? (size_t)n * k : 0;
-    const size_t need = Carver::sz((size_t)k * npad) + Carver::sz((size_t)k * k) +
-                        Carver::sz(sizeof(uint64_t) * (size_t)k * kSmallT * W) + Carver::sz(sizeof(int32_t) * k) * 2 +
-                        Carver::sz(sizeof(int32_t) * (size_t)k * kSmallT) +
-                        Carver::sz(sizeof(int64_t) * (size_t)k * kSmallT) + Carver::sz(sizeof(int64_t) * k) +
-                        Carver::sz(rows) + Carver::sz(want_err ? sizeof(int32_t) * n : 0) + Carver::sz(sizeof(DevFlags)) +
-                        (want_err ? Carver::sz(sweep_scratch_bytes(n, k)) : 0);
+    const bool want_err = wants_errors(*out);
+    const size_t need = small_bytes(n, k, want_err);
     if (L.no_alloc && need > L.arena.size) return false;
     hipStream_t st = L.stream;
     Carver c(L.arena.get(need));
@@ -1522,7 +1539,7 @@ bool run_small(cc_context* ctx, const cc_graph* gr, const Resolved& r, const std
     o.samples = out->samples;
     o.dmat = out->dmat;
     o.D = out->D;
-    o.rows = want_err ? c.take<uint8_t>(rows) : nullptr;
+    o.rows = want_err ? c.take<uint8_t>((size_t)n * k) : nullptr;
     o.sidx = want_err ? c.take<int32_t>(n) : nullptr;
     DevFlags* err_flags = c.take<DevFlags>(1);
     SmallSamples ss;
@@ -3317,7 +3334,7 @@ extern "C" cc_status cc_submit(cc_context* ctx, const cc_graph* g, const cc_para
     j->samples = r.samples;
     j->p.samples = nullptr;
     j->out = *out;
-    j->need = job_bytes(g->dg, r.k, r.mode, g->dg.weighted ? 4 : 1);
+    j->need = job_bytes(g, r, *out);
     j->t_submit = std::chrono::steady_clock::now();
     {
         std::lock_guard<std::mutex> lk(ctx->qmu);

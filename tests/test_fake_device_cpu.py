@@ -111,3 +111,32 @@ def test_upload_keeps_the_patch_tables_it_uses(fake_lib):
         ctx.release(gh)
         assert fake.fake_live() == before
     """)
+
+
+def test_served_jobs_stay_inside_the_budget(fake_lib):
+    """Admission charges a job what it will hold: with room for one search by
+    patches (17 MB at 256 samples, whatever the graph's size), or for one small
+    graph's estimate with its error outputs, four slots run one at a time."""
+    _run(fake_lib, """
+        ctx.close()
+        # (graph, samples, outputs, bytes of one estimate's buffers within a few rounded up to whole MiB)
+        cases = [(graphgen.grid(16, 32, 8, 0.1, 1, 1000, seed=1), 256, ("S_hyb",), 20 << 20),
+                 (graphgen.ba(1000, 4, seed=1), 256, ("S_hyb", "S_err"), 6 << 20)]
+        for g, k, outputs, one in cases:
+            fake.fake_sync_us(0)
+            with cc.Context(0, mem_budget_bytes=one, max_inflight=4) as c:
+                gh = c.upload(g)
+                before = fake.fake_live()
+                fake.fake_reset_peak()
+                fake.fake_sync_us(3000)
+                jobs = [cc.cc_submit(c.handle, gh, k, seed=j, outputs=outputs) for j in range(6)]
+                for j in jobs:
+                    try:
+                        cc.cc_wait(j)
+                    except cc.CCError:  # nothing ran
+                        pass
+                    cc.cc_job_release(j)
+                held = fake.fake_peak() - before
+                assert held <= one, (g.name, held, one)
+                c.release(gh)
+    """)

@@ -2853,6 +2853,8 @@ extern "C" cc_status cc_reach_weighted(cc_context* ctx, const cc_graph* g, const
             return (void*)x;
         };
         ReachArgs a;
+        static_assert(sizeof(L.rb_host->small) >= kReachReadback);
+        a.readback = L.rb_host->small;
         a.n = n;
         a.arcs = g->dg.arcs;
         a.k = p->k;
@@ -2934,6 +2936,8 @@ extern "C" cc_status cc_reach_estimate(cc_context* ctx, const cc_graph* g, const
         const size_t outb = (sizeof(int32_t) + 4 * sizeof(int64_t)) * (size_t)n + 1024;
         char* ob = (char*)L.arena2.get(outb);
         ReachArgs a;
+        static_assert(sizeof(L.rb_host->small) >= kReachReadback);
+        a.readback = L.rb_host->small;
         a.n = n;
         a.arcs = g->dg.arcs;
         a.k = p->k;

@@ -655,6 +655,7 @@ void run_beta_epilogue(hipStream_t st, const BetaArgs& a, DevFlags* flags);
 
 // Outbound / inbound reachability sampling (Sec. 6.2, Algorithm 4).
 constexpr int kReachWords = 16;  // up to 1024 sources of consecutive ranks per batch
+constexpr size_t kReachReadback = 512;
 struct ReachArgs {
     int64_t n = 0;
     int64_t arcs = 0;  // propagation arcs (rp[n])
@@ -670,13 +671,7 @@ struct ReachArgs {
     int64_t* T = nullptr;
     double* B = nullptr;
     double* R = nullptr;
-    // R-MAT, 2^20 nodes, k = 100, first batch: a push of 16 M arcs takes 0.94 ms
-    // with 512 blocks and 0.67 with 2048 (latency of chains, wanted: waves); the
-    // merge's stores are no faster with 1024 than with 128 blocks; the account of
-    // 10^6 nodes takes 0.96 ms with 64 blocks, 0.31 with 512, 0.40 with 1024.
-    int32_t push_blocks = 2048;
-    int32_t merge_blocks = 128;
-    int32_t account_blocks = 512;
+    void* readback = nullptr;  // pinned, kReachReadback bytes: where the run's control block is looked at
     // node-weighted sampling (Algorithm 5): order lists only the nsrc nodes of
     // positive weight; beta and U (priority-rank numerators) per internal id, on
     // the device; outputs count, kth (the k-th member), S_w and R

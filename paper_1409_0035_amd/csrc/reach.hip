@@ -41,6 +41,8 @@
 // once.
 #include "internal.h"
 
+#include <cstring>
+
 namespace ccg {
 
 namespace {
@@ -79,6 +81,7 @@ struct ReachCtl {
     int64_t levels;  // levels run, all batches
     int64_t nact;    // sources with propagation arcs (the list's length)
 };
+static_assert(sizeof(ReachCtl) <= kReachReadback);
 
 struct ReachView {
     int64_t n;
@@ -1383,6 +1386,18 @@ __global__ void k_rl_fill64(uint64_t* p, int64_t count, uint64_t v) {
 
 }  // namespace
 
+// Blocks of a launch, which is made in every cycle, idle or not: as many as the
+// graph's widest level or account fills.  R-MAT, 2^20 nodes, k = 100, first
+// batch: a push of 16 M arcs takes 0.94 ms with 512 blocks and 0.67 with 2048
+// (latency of chains, wanted: waves), the account of 10^6 nodes 0.96 ms with 64
+// blocks, 0.31 with 512, 0.40 with 1024; the merge's stores are no faster with
+// 1024 than with 128 blocks.  On small frontiers the idle blocks count: 400 x 400
+// grid, k = 4, 24.5 ms with 2048 and 512 blocks, 18.8 with 620 and 512; 30,000
+// nodes of 8 arcs 0.87 / 0.73.
+static unsigned push_blocks(int64_t arcs) { return (unsigned)std::clamp<int64_t>(arcs / 2048, 512, 2048); }
+static unsigned account_blocks(int64_t n) { return (unsigned)std::clamp<int64_t>(n / 256, 64, 512); }
+constexpr unsigned kMergeBlocks = 128;
+
 size_t reach_scratch_bytes(int64_t n, int64_t arcs, int32_t k_weighted) {
     constexpr int W = kReachWords;
     auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
@@ -1506,7 +1521,7 @@ static void run_reach_lengths(hipStream_t st, const ReachArgs& a, void* scratch,
     hipLaunchKernelGGL(k_rch_set_phase, dim3(1), dim3(1), 0, st, &lc->rc, (int32_t)kLSearch);
     CCG_HIP(hipGetLastError());
 
-    const unsigned ga = (unsigned)std::max(1, a.account_blocks);
+    const unsigned ga = account_blocks(n);
     const int64_t max_cycles = R.nsrc + 64;  // every batch but the last takes at least one source; the list is weeded at doubling batch counts
     int64_t cycles = 0;
     int32_t chunk = 4;
@@ -1518,8 +1533,9 @@ static void run_reach_lengths(hipStream_t st, const ReachArgs& a, void* scratch,
         }
         CCG_HIP(hipGetLastError());
         cycles += chunk;
-        CCG_HIP(hipMemcpyAsync(&hc, lc, sizeof(hc), hipMemcpyDeviceToHost, st));
+        CCG_HIP(hipMemcpyAsync(a.readback, lc, sizeof(hc), hipMemcpyDeviceToHost, st));
         CCG_HIP(hipStreamSynchronize(st));
+        std::memcpy(&hc, a.readback, sizeof(hc));
         if (hc.rc.phase == kLFinished || hc.rc.overflow || hc.timeout) break;
         if (cycles > max_cycles) throw HipError{hipErrorLaunchTimeOut, "reachability sampling did not finish"};
         if (chunk < 64) chunk *= 2;
@@ -1531,8 +1547,9 @@ static void run_reach_lengths(hipStream_t st, const ReachArgs& a, void* scratch,
         else
             hipLaunchKernelGGL(k_rch_out, dim3(gn), dim3(256), 0, st, R, a.orig, a.count, a.distsum, a.T, a.B, a.R);
         CCG_HIP(hipGetLastError());
-        CCG_HIP(hipMemcpyAsync(&hc, lc, sizeof(hc), hipMemcpyDeviceToHost, st));
+        CCG_HIP(hipMemcpyAsync(a.readback, lc, sizeof(hc), hipMemcpyDeviceToHost, st));
         CCG_HIP(hipStreamSynchronize(st));
+        std::memcpy(&hc, a.readback, sizeof(hc));
     }
     if (stats) {
         stats->cycles = cycles;
@@ -1621,11 +1638,11 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
     hipLaunchKernelGGL(k_rch_set_phase, dim3(1), dim3(1), 0, st, ctl, (int32_t)kAccount);
     CCG_HIP(hipGetLastError());
 
-    const unsigned gp = (unsigned)a.push_blocks, gm = (unsigned)a.merge_blocks, ga = (unsigned)a.account_blocks;
+    const unsigned gp = push_blocks(a.arcs), gm = kMergeBlocks, ga = account_blocks(n);
     const int64_t nbatches = (V.nsrc + kFirstBatch - 1) / kFirstBatch + 1;
     const int64_t max_cycles = nbatches * (n + 2);
     int64_t cycles = 0;
-    int32_t chunk = 8;
+    int32_t chunk = 12;
     ReachCtl hc{};
     for (;;) {
         for (int32_t c = 0; c < chunk; c++) {
@@ -1635,12 +1652,16 @@ void run_reach(hipStream_t st, const ReachArgs& a, void* scratch, size_t scratch
         }
         CCG_HIP(hipGetLastError());
         cycles += chunk;
-        CCG_HIP(hipMemcpyAsync(&hc, ctl, sizeof(hc), hipMemcpyDeviceToHost, st));
+        CCG_HIP(hipMemcpyAsync(a.readback, ctl, sizeof(hc), hipMemcpyDeviceToHost, st));
         CCG_HIP(hipStreamSynchronize(st));
+        std::memcpy(&hc, a.readback, sizeof(hc));
         if (hc.phase == kFinished) break;
         if (cycles > max_cycles) throw HipError{hipErrorLaunchTimeOut, "reachability sampling did not finish"};
-        // most estimates end within three dozen cycles; an idle one costs three launches
-        if (cycles >= 32 && chunk < 256) chunk *= 2;
+        // looked at after 12, 24, 48, 112, 240, ... cycles: graphs of small diameter
+        // end within 12 or, weeded, within 24, and a look costs about what ten
+        // idle cycles do (looks after 8, 16, 24, 32, ...: 1,000 nodes of 4 arcs
+        // 468 us, R-MAT scale 14 649; now 380 and 532)
+        if (cycles > 12) chunk = std::min(cycles == 48 ? 64 : chunk * 2, 256);
     }
     if (weighted)
         hipLaunchKernelGGL(k_rch_out_beta<uint16_t>, dim3(gn), dim3(256), 0, st, V, (const uint16_t*)V.mem_d, a.orig,

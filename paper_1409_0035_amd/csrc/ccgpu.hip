@@ -2401,9 +2401,14 @@ constexpr int32_t kMaxOvertakes = 16;          // younger jobs that may pass a w
 constexpr int32_t kBatchWords = 4;
 
 bool batchable(const cc_graph* g, const Resolved& r) {
-    // a small graph's own two launches cost less than its share of a shared traversal
-    return !small_search_fits(g, r) && !g->borrowed && !g->dg.directed && !g->dg.weighted && r.mode == CC_BATCHED && r.k <= 192 && g->dg.n <= kBatchNodeLimit &&
-           g->dg.arcs < ((int64_t)1 << 30);
+    // A small graph's own two launches cost less than its share of a shared
+    // traversal (us a job, shared / alone, first one cc_estimate_batch of 16-64
+    // jobs, then the same submitted to four slots: 200 nodes, k = 16 136 / 53 and
+    // 56 / 17; 1,000 nodes, k = 64 148 / 59 and 49 / 16; grid of 1,200 nodes 1000 /
+    // 221 and 402 / 58; 10,000 nodes, k = 64 196 / 86 and 71 / 28; R-MAT scale 16,
+    // k = 64 250 / 238 and 131 / 101).
+    return !small_search_fits(g, r) && !g->borrowed && !g->dg.directed && !g->dg.weighted && r.mode == CC_BATCHED &&
+           r.k <= 192 && g->dg.n <= kBatchNodeLimit && g->dg.arcs < ((int64_t)1 << 30);
 }
 
 __global__ void k_union_copy(const uint32_t* __restrict__ rp, const int32_t* __restrict__ col, int64_t n, int64_t npad,

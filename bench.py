@@ -369,6 +369,18 @@ def reach_bench(args, graphgen, cc, torch):
     ctx.close()
 
 
+def small_roofline(timings, k: int) -> dict:
+    """The search of a small graph: one launch of one workgroup per sample.
+    Bound by the latency of its levels; its bytes are 4 per arc read (the arcs
+    each sample reads for itself, from a cache for the most part)."""
+    us = sum(t["kernel_ms"] for t in timings) / len(timings) * 1e3
+    arcs = sum(t["arcs_scanned"] for t in timings) / len(timings)
+    achieved = 4 * arcs / us / 1e3
+    return {"bound": "latency", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": None, "kernel": "k_small_search",
+            "avg_launch_us": round(us, 2), "launches_per_step": 1, "arcs_per_sample": round(arcs / k, 1)}
+
+
 def wsearch_roofline(timings, workload: str, n: int, arcs: int, k: int, tuning: dict) -> dict:
     """Per-launch algorithmic bytes / average launch duration of the weighted
     searches' kernel (one launch of one workgroup per sample, or rounds over
@@ -494,7 +506,9 @@ def run_config(name, cc, graphgen, torch, steps, warmup, plain_steps, autotune=T
             step(cc.CC_BATCHED)
             timings.append(cc.cc_last_timing(ctx.handle))
     tm = timings[-1]
-    if g.w is None:
+    if all(t["search"] == cc.CC_SEARCH_SMALL for t in timings):
+        roofline = small_roofline(timings, k)
+    elif g.w is None:
         W = (min(k, 256) + 63) // 64
         roofline = scatter_roofline(timings, W, name, tuning)
     else:

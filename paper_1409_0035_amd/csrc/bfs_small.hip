@@ -4,8 +4,8 @@
 // on a graph whose arcs and masks sit in a few CUs' reach every launch is a
 // chain of dependent round trips with most of the device idle (10,000 nodes,
 // 80,000 arcs, 64 samples: 14 level launches of 4-17 us, 181-189 us an
-// estimate even when replayed; 72 us this way, the searches 40 and the
-// estimates 6 of it).  Here each of the k searches of Sec. 3 of the paper runs in a
+// estimate even when replayed; 72 us this way, the searches 43 and the
+// estimates 7 of it).  Here each of the k searches of Sec. 3 of the paper runs in a
 // workgroup of its own, with the node's distance (one byte), the visited bits
 // and the frontier in LDS, so a level costs a barrier instead of two
 // launches, and one launch does all searches.  The same workgroup then has
@@ -20,7 +20,7 @@
 //
 // A level pushes from its frontier (a list in LDS whose arcs are dealt to the
 // threads by a prefix sum of the degrees, so a hub costs what its arcs cost)
-// while the frontier's arcs are few; otherwise it pulls:
+// while the frontier's arcs are fewer than a pull would read; otherwise it pulls:
 // a lane per unvisited node reads its arcs four at a time until one of them
 // ends at a node of an earlier level, which the triangle argument of
 // bfs_batched.hip makes the previous level.  Lanes left after 64 arcs finish

@@ -15,3 +15,10 @@ def test_weighted_roofline_names_the_search_that_ran():
     assert bench.wsearch_roofline(two, "none", 100, 700, 4, TUNING)["kernel"] == "k_wsearch"
     rounds = [_timing(cc.CC_SEARCH_PATCHES, 40)] * 3
     assert bench.wsearch_roofline(rounds, "none", 100, 700, 4, TUNING)["kernel"] == "k_patch_round"
+
+
+def test_small_graph_roofline_counts_the_arcs_read():
+    t = dict(kernel_ms=0.04, arcs_scanned=2_000_000, search=cc.CC_SEARCH_SMALL)
+    r = bench.small_roofline([t, t], 64)
+    assert r["kernel"] == "k_small_search" and r["launches_per_step"] == 1
+    assert r["achieved"] == 200.0 and r["arcs_per_sample"] == 31250.0

@@ -472,7 +472,8 @@ struct cc_graph {
     std::vector<int32_t> chunks_host;  // hub chunk triples (undirected graphs), for batching
     bool borrowed = false;  // the arcs (and lengths) are the caller's device arrays, never freed here
     mutable std::atomic<int32_t> bfs_hint{0};  // levels the last batched traversal of this graph ran
-    mutable std::atomic<int32_t> patch_hint[2] = {{0}, {0}};  // rounds the last searches by patches ran, by direction
+    // rounds the last searches by patches ran, by direction, under the step they had: step << 32 | rounds
+    mutable std::atomic<uint64_t> patch_hint[2] = {{0}, {0}};
     mutable std::atomic<bool> patch_off{false};  // distances too large for the searches by patches
     mutable std::atomic<uint32_t> patch_short{0};  // the widest step (it follows the tuning) at which their rounds ran out
     mutable std::atomic<bool> small_deep{false};  // a distance passed 254: the small-graph searches cannot hold it
@@ -1849,6 +1850,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
         // ---- traversal
         int rc = 0;
         int32_t lmax_dir[2] = {0, 0};
+        int32_t patch_ran[2] = {0, 0};   // rounds each direction's searches by patches ran
         int32_t levels_dir[2] = {0, 0};  // levels each direction's batched traversal ran
         bool rt_summed = false;          // D holds the round-trip distances (no separate reverse array)
         // a round trip of one sample group, after both searches: with one-byte
@@ -1885,10 +1887,12 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                     shape.local_passes = gr->tune.local_passes;
                     int wr = 0;
                     if (patched) {
-                        int32_t hint = gr->patch_hint[dir].load(std::memory_order_relaxed);
+                        const uint64_t last = gr->patch_hint[dir].load(std::memory_order_relaxed);
+                        int32_t hint = last >> 32 == patch_step ? (int32_t)(uint32_t)last : 0;
                         wr = sssp_patch(st, g.patches, dir, n, samples_dev + s0, kg, (uint32_t*)Dt + (size_t)s0 * n,
                                         patch_step, ts, trav_scratch, &hint, &md, &ds);
-                        gr->patch_hint[dir].store(hint, std::memory_order_relaxed);
+                        patch_ran[dir] = hint;
+                        gr->patch_hint[dir].store((uint64_t)patch_step << 32 | (uint32_t)hint, std::memory_order_relaxed);
                         if (wr == 4) gr->patch_off.store(true, std::memory_order_relaxed);
                         if (wr == 6) {
                             uint32_t seen = gr->patch_short.load(std::memory_order_relaxed);
@@ -2102,7 +2106,7 @@ cc_status run_job(cc_context* ctx, const cc_graph* gr, const Resolved& r, const 
                 for (int dir = 0; dir < (g.directed ? 2 : 1); dir++) {
                     if (patched) {
                         // a quarter more rounds than this search ran: other samples' searches reach about as far
-                        const int32_t ran = gr->patch_hint[dir].load(std::memory_order_relaxed);
+                        const int32_t ran = patch_ran[dir];
                         sssp_patch_enqueue(st, g.patches, dir, n, samples_dev, k, (uint32_t*)Dt, patch_step, ts,
                                            trav_scratch, ran + ran / 4 + 4, flags, wmaxd_dev + dir);
                     } else {

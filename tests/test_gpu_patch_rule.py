@@ -134,3 +134,25 @@ def test_groups_of_samples(k):
     """Few patches: samples in 8, 16, 32 or 64 groups (more from 40, 80, 160 samples
     on, four a group at least), the last samples of a group missing."""
     _check(graphgen.grid(20, 33, 8, 0.1, 1, 1000, seed=5), k, cc.CC_SEARCH_PATCHES)
+
+
+def test_first_look_after_a_change_of_step():
+    """The rounds that a search enqueues before its first look are those of the
+    last search at the same bucket width: after one at width 1, which runs
+    thousands, an estimate at the default width enqueues its own few."""
+    g = graphgen.grid(300, 300, 8, 0.1, 1, 1_000_000, seed=2)
+    with cc.Context(0) as ctx:
+        gh = ctx.upload(g)
+        width = cc.cc_graph_get_tuning(gh)["delta"]
+        seen = []
+        for delta in (width, 1, width, width):
+            cc.cc_graph_set_tuning(gh, delta=delta)
+            cc.cc_estimate(ctx.handle, gh, 2, seed=1, outputs=("delta",))
+            t = cc.cc_last_timing(ctx.handle)
+            assert t["search"] == cc.CC_SEARCH_PATCHES
+            seen.append((t["levels"], t["launches"]))
+        print(f"  rounds and launches {seen}")
+        assert seen[1][0] > 10 * seen[0][0]
+        # looks come after 16 rounds and half as many again each time, then once after the rounds of the last call
+        assert seen[2][1] <= 2 * seen[2][0] + 40 and seen[3][1] <= seen[3][0] + 40
+        ctx.release(gh)

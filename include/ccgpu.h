@@ -292,7 +292,7 @@ cc_status cc_graph_set_tuning(cc_graph* g, const cc_tuning* t);
  * the fastest setting in the graph and returns it with its time (ms, device
  * time of one estimate); a small graph's search (CC_BATCHED) reads no knob, so
  * its setting is only timed; a candidate replaces the current setting only when it
- * is at least 3% faster, so that timing noise does not move the setting.  Uses
+ * is at least 5% faster, so that timing noise does not move the setting.  Uses
  * the context's own stream and device buffers it allocates and frees itself. */
 cc_status cc_autotune(cc_context* ctx, cc_graph* g, int32_t k, uint64_t seed, int32_t reps, cc_tuning* best,
                       double* best_ms);
